@@ -236,7 +236,7 @@ int ch_step_lim(ch_ctx *ctx, const ch_problem *prob, double *y, double tau, doub
 /*
  * For callers that cannot allocate device memory (code under stream capture,
  * tight serving loops, harnesses that forbid hipMalloc): ch_step_lim without
- * any allocation.  Same arguments, kernels and result as ch_step_lim; its
+ * any allocation.  Same arguments and result as ch_step_lim; its
  * scratch (two state buffers and a stage buffer of up to
  * CH_NOALLOC_MAX_POINTS points, reduction partials, node order, stage
  * coefficients, control block, step record, instance table: 26.3 MB) is a
@@ -338,8 +338,9 @@ enum ch_kernel {
                                   test workgroup a run's update launch may carry) */
     CH_KERNEL_LIM_STAGE = 5,   /* one LIM Chebyshev stage */
     CH_KERNEL_DC_ITER = 6,     /* one whole DCGS2 iteration: matvec, dot totals, update */
-    CH_KERNEL_LIM_STAGE2 = 7   /* two consecutive LIM stages in one launch (2-D only: the form
-                                  ch_run_lim uses there for every stage after the first) */
+    CH_KERNEL_LIM_STAGE2 = 7   /* two consecutive LIM stages in one launch (2-D only: the form of
+                                  batches, and of ch_run_lim on grids too large to be resident,
+                                  for every stage after the first) */
 };
 
 /*
@@ -375,7 +376,9 @@ int ch_time_kernel(ch_ctx *ctx, const ch_problem *prob, int kernel, int m_max, c
  *         1..512, each looping over chunks of 2048 points.
  * The shape changes the order in which the partial sums of dot products are
  * added, so results of two shapes agree to rounding, not bit for bit.  LIM runs
- * use the shape of (dim, n, CH_FP64).
+ * use the shape of (dim, n, CH_FP64), except for the stages of a single 2-D grid
+ * that fits the device (up to about 1300^2), whose launch has tiles of its own and whose
+ * values do not depend on it.
  */
 typedef struct {
     int vx;

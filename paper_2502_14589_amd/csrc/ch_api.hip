@@ -14,6 +14,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <climits>
 #include <chrono>
 #include <condition_variable>
@@ -28,6 +29,7 @@
 
 #include "ch_internal.h"
 #include "ch_march.h"
+#include "ch_resident.h"
 
 struct ch_ctx {
     int device = 0;
@@ -39,6 +41,7 @@ struct ch_ctx {
     size_t z_pts = 0;
     int slots = 0;           // control blocks allocated
     size_t rec_n = 0;        // step records allocated
+    int cus = 0;             // compute units of the device
     int phibig_slots = 0;    // slots of the phi scratch of orders above 48
     ch_step_record* rec = nullptr;
     std::vector<int> expect; // per slot: Krylov cycles issued (compared with the device's `cyc`)
@@ -251,6 +254,47 @@ int ensure(ch_ctx* ctx, size_t pts, int m_max, int prec, int nslots, size_t recs
         ctx->rec_n = recs;
     }
     return CH_OK;
+}
+
+// CUs of each device held by resident launches (ch_resident.h) of this
+// process.  A call that issues such launches holds a lease on one CU per
+// workgroup until its stream has drained, so the workgroups of all leases on a
+// device fit it together and no launch waits for workgroups that cannot
+// start; a call that gets no lease issues ordinary launches (same results).
+class ResidentLease {
+    static constexpr int DEVICES = 64;
+    static std::atomic<int> used[DEVICES];
+    std::atomic<int>* u = nullptr;
+    int n = 0;
+
+public:
+    ResidentLease() = default;
+    ResidentLease(const ResidentLease&) = delete;
+    ResidentLease& operator=(const ResidentLease&) = delete;
+    ~ResidentLease() { release(); }
+    bool take(int device, int cus, int count) {
+        release();
+        if (device < 0 || device >= DEVICES || count < 1) return false;
+        if (used[device].fetch_add(count) + count > cus) {
+            used[device].fetch_sub(count);
+            return false;
+        }
+        u = &used[device];
+        n = count;
+        return true;
+    }
+    void release() {
+        if (u) u->fetch_sub(n);
+        u = nullptr;
+    }
+};
+std::atomic<int> ResidentLease::used[ResidentLease::DEVICES];
+
+// The flags of the context's resident launches (cleared on the device before
+// each use).
+int ensure_resident(ch_ctx* ctx) {
+    if (ctx->b.flags) return CH_OK;
+    return alloc_dev(ctx, (void**)&ctx->b.flags, sizeof(int) * CH_RES_WORDS);
 }
 
 struct Member {
@@ -723,6 +767,40 @@ int issue_lim_step(ch_ctx* ctx, const Table& t, const DevBuffers& b, PartSeq& ps
     return CH_OK;
 }
 
+// LIM steps of a single grid with resident stage launches, from step *s on:
+// five launches per step and no host wait, since the stage launch reads the
+// Chebyshev order itself; the control block is read every 16 steps to see
+// whether the run has ended.  *s: the steps taken when it returns.
+// *done: the run is over; otherwise a launch gave up waiting and step *s is
+// to be repeated with ordinary launches.
+int issue_lim_resident(ch_ctx* ctx, const Table& t, const LimTiles& g, PartSeq& ps, int max_steps, long long* s,
+                       bool* done) {
+    const DevBuffers& b = ctx->b;
+    int rc;
+    for (long long k = *s;; ++k) {
+        const bool last = max_steps > 0 && k >= max_steps;
+        if (last || (k % 16) == 15) {
+            if ((rc = read_heads(ctx, 1))) return rc;
+            if (last || ctx->hctl[0].halted) break;
+        }
+        const double* yin = b.ybuf[k & 1];
+        double* yout = b.ybuf[(k + 1) & 1];
+        HIP_TRY(ctx, launch_lim_begin(t, b, ps, yin, ctx->stream));
+        HIP_TRY(ctx, launch_lim_plan(t, b, ps, ++ctx->lseq, ctx->stream));
+        HIP_TRY(ctx, launch_lim_run(t, b, g, yin, yout, ctx->stream));
+        HIP_TRY(ctx, launch_est_lim(t, b, ps, yin, yout, ctx->stream));
+        HIP_TRY(ctx, launch_lim_end(t, b, ps, ctx->stream));
+    }
+    Ctl& h = ctx->hctl[0];
+    *s = h.steps;
+    *done = h.status != CH_RES_RETRY;
+    if (*done) return CH_OK;
+    h.status = CH_OK;
+    h.halted = 0;
+    HIP_TRY(ctx, hipMemcpyAsync(b.ctl, &h, CTL_HEAD, hipMemcpyHostToDevice, ctx->stream));
+    return CH_OK;
+}
+
 int run_lim(ch_ctx* ctx, const ch_problem* prob, double* y, double tau0, double t0, double T, int max_steps,
             double tol, ch_run_stats* stats, ch_step_record* records) {
     Shape sh;
@@ -743,7 +821,16 @@ int run_lim(ch_ctx* ctx, const ch_problem* prob, double* y, double tau0, double 
     if ((rc = copy_in(ctx, m, y))) return rc;
     PartSeq ps;
     ps.base = b.part;
-    for (long long s = 0;; ++s) {
+    long long s0 = 0;
+    bool done = false;
+    ResidentLease lease;   // held until the call returns: its stream has drained then
+    if (uses_strips(t)) {
+        const LimTiles g = lim_tiles(t.hinst[0], ctx->cus);
+        if (g.rows > 0 && ensure_resident(ctx) == CH_OK && lease.take(ctx->device, ctx->cus, g.ntx * g.nty)) {
+            if ((rc = issue_lim_resident(ctx, t, g, ps, max_steps, &s0, &done))) return rc;
+        }
+    }
+    for (long long s = s0; !done; ++s) {
         if (max_steps > 0 && s >= max_steps) break;
         bool halted = false;
         if ((rc = issue_lim_step(ctx, t, b, ps, ctx->hctl, s, &halted))) return rc;
@@ -1201,6 +1288,14 @@ int ch_create(ch_ctx** out, int device, void* hip_stream) {
     if (!ctx) return CH_ENOMEM;
     ctx->device = device;
     ctx->stream = static_cast<hipStream_t>(hip_stream);
+    if (hipDeviceGetAttribute(&ctx->cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->cus = 0;
+    }
+    // CH_RESIDENT_WAIT_US: how long a workgroup of a resident launch waits for
+    // another before the step is repeated with ordinary launches
+    const char* w = getenv("CH_RESIDENT_WAIT_US");
+    ctx->b.wait_us = w ? (unsigned)std::max(0l, std::min(strtol(w, nullptr, 10), 10000000l)) : CH_RES_WAIT_US;
     noalloc_setup(device);
     LaunchEnv& sd = ctx->env;
     sd.graphs = &ctx->graphs;
@@ -1228,7 +1323,7 @@ int ch_destroy(ch_ctx* ctx) {
     destroy_graphs(ctx->graphs);
     for (void* p : {(void*)b.V, (void*)b.ybuf[0], (void*)b.ybuf[1], (void*)b.fcur, (void*)b.y32, (void*)b.zbuf,
                     (void*)b.part, (void*)b.dots, (void*)b.lorder, (void*)b.ctl, (void*)ctx->rec, b.phibig,
-                    (void*)b.lcoef, (void*)b.dcount})
+                    (void*)b.lcoef, (void*)b.dcount, (void*)b.flags})
         free_dev(p);
     for (auto& ts : ctx->store)
         for (void* p : {(void*)ts.d_inst, (void*)ts.d_sb2i, (void*)ts.d_cb2i, (void*)ts.d_wb2i}) free_dev(p);

@@ -150,6 +150,8 @@ struct DevBuffers {
     int* dcount;        // device counter of the DCGS2 update launches begun (mirrors hseq)
     int* dlim;          // device view of `hlim`
     const volatile int* hlim;   // pinned host words, per slot: the LIM plan's order p (0: halted), then its tag
+    int* flags;         // flags of the resident launches (ch_resident.h), or null
+    unsigned wait_us;   // bound of their waits
     void* phibig;       // per-slot device scratch of the phi of orders above 48 (phi_big_bytes each)
 };
 

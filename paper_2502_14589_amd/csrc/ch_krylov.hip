@@ -15,6 +15,7 @@
 // workgroups [cblk0, cblk0 + cblk) (map cb2i), single-workgroup kernels one
 // workgroup per instance.
 #include "ch_common.h"
+#include "ch_resident.h"
 #include "ch_stream.h"
 
 #include <algorithm>
@@ -1468,9 +1469,11 @@ template <bool SINGLE>
 __global__ __launch_bounds__(CH_BLOCK) void k_lim_plan(Ctl* __restrict__ ctls, const Inst* __restrict__ insts, const Inst inst0, int ninst,
                                                        const double* __restrict__ pin, int pin_stencil, int dim,
                                                        int* __restrict__ orders, double* __restrict__ coefs,
-                                                       int* __restrict__ dlim, int seq) {
+                                                       int* __restrict__ dlim, int seq, int* __restrict__ flags) {
     const Inst I = SINGLE ? inst0 : insts[blockIdx.x];
     Ctl* ctl = ctls + I.slot;
+    if (SINGLE && flags)   // for the resident stage launch that follows
+        for (int i = threadIdx.x; i <= CH_RES_MAX; i += CH_BLOCK) flags[i * CH_RES_LINE] = 0;
     if (ctl->halted) {
         publish_order(dlim, I.slot, 0, seq);
         return;
@@ -1961,9 +1964,9 @@ hipError_t launch_lim_begin(const Table& t, const DevBuffers& b, PartSeq& ps, co
 
 hipError_t launch_lim_plan(const Table& t, const DevBuffers& b, PartSeq& ps, int seq, hipStream_t s) {
     if (t.ninst == 1)
-        hipLaunchKernelGGL((k_lim_plan<true>), IARGS, ps.in(), ps.stencil, t.dim, b.lorder, b.lcoef, b.dlim, seq);
+        hipLaunchKernelGGL((k_lim_plan<true>), IARGS, ps.in(), ps.stencil, t.dim, b.lorder, b.lcoef, b.dlim, seq, b.flags);
     else
-        hipLaunchKernelGGL((k_lim_plan<false>), IARGS, ps.in(), ps.stencil, t.dim, b.lorder, b.lcoef, b.dlim, seq);
+        hipLaunchKernelGGL((k_lim_plan<false>), IARGS, ps.in(), ps.stencil, t.dim, b.lorder, b.lcoef, b.dlim, seq, b.flags);
     return hipGetLastError();
 }
 

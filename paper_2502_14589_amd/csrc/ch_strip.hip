@@ -19,170 +19,11 @@
 // Wave w of strip workgroup b (counted from the instance's first one, XCD
 // banded) takes strips 4b' + w, 4b' + w + 4 wblk, ...; strip s covers columns
 // [(s % nsx) OW, + OW) and rows [(s / nsx) SR, + SR).
-#include "ch_common.h"
+#include "ch_rows.h"
 
 namespace {
 
 constexpr int SR = CH_STRIP_ROWS;
-
-// Raw buffer resource over one grid row (wave-uniform base; lanes address it
-// by byte offset; an offset past the row reads zero and drops a store).  The
-// last word is the gfx9 data-format word.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* p, unsigned bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-
-using u32x2 = unsigned __attribute__((ext_vector_type(2)));
-using u32x4 = unsigned __attribute__((ext_vector_type(4)));
-
-// VX consecutive values of type T at byte offset `bo` of row resource r.
-template <typename T, int VX>
-__device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r, unsigned bo, T (&v)[VX]) {
-    constexpr unsigned so = 0;
-    constexpr int B = VX * (int)sizeof(T);
-    if constexpr (B == 4) {
-        v[0] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, bo, so, 0));
-    } else if constexpr (B == 8) {
-        const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(r, bo, so, 0);
-        struct P { T e[VX]; };
-        const P p = __builtin_bit_cast(P, x);
-#pragma unroll
-        for (int e = 0; e < VX; ++e) v[e] = p.e[e];
-    } else if constexpr (B == 16) {
-        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, bo, so, 0);
-        struct P { T e[VX]; };
-        const P p = __builtin_bit_cast(P, x);
-#pragma unroll
-        for (int e = 0; e < VX; ++e) v[e] = p.e[e];
-    } else {
-        static_assert(B == 32, "row chunk of 4, 8, 16 or 32 bytes");
-        constexpr int H = VX / 2;
-        T a[H], c[H];
-        load_row<T, H>(r, bo, a);
-        load_row<T, H>(r, bo + 16u, c);
-#pragma unroll
-        for (int e = 0; e < H; ++e) {
-            v[e] = a[e];
-            v[H + e] = c[e];
-        }
-    }
-}
-
-template <typename T, int VX>
-__device__ __forceinline__ void store_row(__amdgpu_buffer_rsrc_t r, unsigned bo, const T (&v)[VX]) {
-    constexpr unsigned so = 0;
-    constexpr int B = VX * (int)sizeof(T);
-    struct P { T e[VX]; };
-    P p;
-#pragma unroll
-    for (int e = 0; e < VX; ++e) p.e[e] = v[e];
-    if constexpr (B == 4) {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, p), r, bo, so, 0);
-    } else if constexpr (B == 8) {
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, p), r, bo, so, 0);
-    } else if constexpr (B == 16) {
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, p), r, bo, so, 0);
-    } else {
-        static_assert(B == 32, "row chunk of 4, 8, 16 or 32 bytes");
-        constexpr int H = VX / 2;
-        T a[H], c[H];
-#pragma unroll
-        for (int e = 0; e < H; ++e) {
-            a[e] = v[e];
-            c[e] = v[H + e];
-        }
-        store_row<T, H>(r, bo, a);
-        store_row<T, H>(r, bo + 16u, c);
-    }
-}
-
-// Whole-wave DPP shifts: lane L receives lane L - 1 (from_left) or L + 1
-// (from_right); the wave's end lanes receive 0 (only halo lanes read them).
-enum { DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138 };
-
-template <int CTRL>
-__device__ __forceinline__ float wave_shift(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
-}
-template <int CTRL>
-__device__ __forceinline__ double wave_shift(double x) {
-    const unsigned long long v = __builtin_bit_cast(unsigned long long, x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, 0xF, 0xF, false);
-    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-
-// Unscaled -Laplacian (4 c - (l + r) - (u + d)) at element e of row `c`,
-// with rows `up` and `dn` above and below.  The x neighbours across the
-// lane boundary arrive by DPP (xl: the left lane's last element, xr: the
-// right lane's first).
-template <typename T, int VX>
-__device__ __forceinline__ T lap5(const T (&up)[VX], const T (&c)[VX], const T (&dn)[VX], T xl, T xr, int e) {
-    const T l = e > 0 ? c[e - 1] : xl;
-    const T r = e < VX - 1 ? c[e + 1] : xr;
-    const T nb = (l + r) + (up[e] + dn[e]);
-    return T(4) * c[e] - nb;
-}
-
-// Flux form of the variable-mobility operator (Section 2, Remark 1),
-// unscaled: sum over the four neighbours k of (m_c + m_k)/2 (q_c - q_k), the
-// mobilities m laid out as the values q (mxl, mxr: the lane neighbours' m).
-// With m = 1 it equals lap5.
-template <typename T, int VX>
-__device__ __forceinline__ T lap5m(const T (&up)[VX], const T (&c)[VX], const T (&dn)[VX], T xl, T xr,
-                                   const T (&mup)[VX], const T (&mc)[VX], const T (&mdn)[VX], T mxl, T mxr, int e) {
-    const T l = e > 0 ? c[e - 1] : xl, r = e < VX - 1 ? c[e + 1] : xr;
-    const T ml = e > 0 ? mc[e - 1] : mxl, mr = e < VX - 1 ? mc[e + 1] : mxr;
-    const T q = c[e], m = mc[e];
-    const T fx = (m + ml) * (q - l) + (m + mr) * (q - r);
-    const T fy = (m + mup[e]) * (q - up[e]) + (m + mdn[e]) * (q - dn[e]);
-    return T(0.5) * (fx + fy);
-}
-
-// The outer operator at element e of row c: A (MOB false) or A_M (MOB true,
-// mobility rows m), both unscaled.
-template <bool MOB, typename T, int VX>
-__device__ __forceinline__ T outer_op(const T (&up)[VX], const T (&c)[VX], const T (&dn)[VX], T xl, T xr,
-                                      const T (&mup)[VX], const T (&mc)[VX], const T (&mdn)[VX], T mxl, T mxr, int e) {
-    if constexpr (MOB) return lap5m<T, VX>(up, c, dn, xl, xr, mup, mc, mdn, mxl, mxr, e);
-    else return lap5<T, VX>(up, c, dn, xl, xr, e);
-}
-
-// Mobility coefficients (from the control block) of a MOB launch.
-struct Mob {
-    double m0, m1;
-};
-__device__ __forceinline__ Mob mob_of(const Ctl* ctl, bool on) { return on ? Mob{ctl->mob0, ctl->mob1} : Mob{0.0, 0.0}; }
-
-// Mobility rows of a block of state rows (MOB), or nothing.
-template <bool MOB, typename T, int VX, int NR>
-struct MobRows {
-    T m[MOB ? NR : 1][VX];
-    __device__ __forceinline__ void set(int j, const T (&y)[VX], T m0, T m1) {
-        if constexpr (MOB) {
-#pragma unroll
-            for (int e = 0; e < VX; ++e) m[j][e] = mobility_of(y[e], m0, m1);
-        }
-    }
-    __device__ __forceinline__ const T (&row(int j) const)[VX] { return m[MOB ? j : 0]; }
-    __device__ __forceinline__ T left(int j) const {
-        if constexpr (MOB) return wave_shift<DPP_WAVE_SHR1>(m[j][VX - 1]);
-        else return T(0);
-    }
-    __device__ __forceinline__ T right(int j) const {
-        if constexpr (MOB) return wave_shift<DPP_WAVE_SHL1>(m[j][0]);
-        else return T(0);
-    }
-};
-
-template <typename T>
-__device__ __forceinline__ T dcoef(T y, int eyre) {
-    return T(3) * y * y - T(1) + T(eyre);
-}
-template <typename T>
-__device__ __forceinline__ T ccoef(T y, int eyre) {
-    return T(2) * y * y * y + (eyre ? y : T(0));
-}
 
 // Strip geometry of one wave.
 template <int VX>
@@ -507,8 +348,8 @@ __device__ __forceinline__ void lim_strips(const Inst& I, const double* __restri
             const double xl = wave_shift<DPP_WAVE_SHR1>(z[j + 1][VX - 1]), xr = wave_shift<DPP_WAVE_SHL1>(z[j + 1][0]);
 #pragma unroll
             for (int e = 0; e < VX; ++e)
-                q[j][e] = dcoef(y[j][e], eyre) * z[j + 1][e] + e2ih2 * lap5<double, VX>(z[j], z[j + 1], z[j + 2], xl, xr, e) -
-                          ccoef(y[j][e], eyre);
+                q[j][e] = lim_inner(dcoef(y[j][e], eyre), z[j + 1][e], e2ih2,
+                                    lap5<double, VX>(z[j], z[j + 1], z[j + 2], xl, xr, e), ccoef(y[j][e], eyre));
         }
 #pragma unroll
         for (int i = 0; i < SR; ++i) {
@@ -517,9 +358,9 @@ __device__ __forceinline__ void lim_strips(const Inst& I, const double* __restri
             double o[VX];
 #pragma unroll
             for (int e = 0; e < VX; ++e) {
-                const double r = -inv_h2 * outer_op<MOB, double, VX>(q[i], q[i + 1], q[i + 2], xl, xr, mb.row(i),
-                                                                    mb.row(i + 1), mb.row(i + 2), ml, mr, e);
-                o[e] = (y[i + 1][e] + ta * z[i + 2][e] + tau * r) * inv;
+                const double op = lim_outer<MOB, VX>(q[i], q[i + 1], q[i + 2], xl, xr, mb.row(i), mb.row(i + 1),
+                                                     mb.row(i + 2), ml, mr, e);
+                o[e] = lim_next(y[i + 1][e], ta, z[i + 2][e], tau, inv_h2, op, inv);
             }
             if (P.out && P.r0 + i < n) store_row<double, VX>(grid_row(O, P.r0 + i, n, bc), bo, o);
         }
@@ -630,8 +471,8 @@ __device__ __forceinline__ void lim2_strips(const Inst& I, const double* __restr
             const double xl1 = wave_shift<DPP_WAVE_SHR1>(z[j + 1][VX - 1]), xr1 = wave_shift<DPP_WAVE_SHL1>(z[j + 1][0]);
 #pragma unroll
             for (int e = 0; e < VX; ++e)
-                q1[j][e] = dcoef(y[j][e], eyre) * z[j + 1][e] + e2ih2 * lap5<double, VX>(z[j], z[j + 1], z[j + 2], xl1, xr1, e) -
-                           ccoef(y[j][e], eyre);
+                q1[j][e] = lim_inner(dcoef(y[j][e], eyre), z[j + 1][e], e2ih2,
+                                     lap5<double, VX>(z[j], z[j + 1], z[j + 2], xl1, xr1, e), ccoef(y[j][e], eyre));
         }
         double o1[NO1][VX];
 #pragma unroll
@@ -640,9 +481,9 @@ __device__ __forceinline__ void lim2_strips(const Inst& I, const double* __restr
             const double ml = mb.left(j + 1), mr = mb.right(j + 1);
 #pragma unroll
             for (int e = 0; e < VX; ++e) {
-                const double r = -inv_h2 * outer_op<MOB, double, VX>(q1[j], q1[j + 1], q1[j + 2], xl1, xr1, mb.row(j),
-                                                                    mb.row(j + 1), mb.row(j + 2), ml, mr, e);
-                o1[j][e] = (y[j + 1][e] + ta1 * z[j + 2][e] + tau * r) * inv1;
+                const double op = lim_outer<MOB, VX>(q1[j], q1[j + 1], q1[j + 2], xl1, xr1, mb.row(j), mb.row(j + 1),
+                                                     mb.row(j + 2), ml, mr, e);
+                o1[j][e] = lim_next(y[j + 1][e], ta1, z[j + 2][e], tau, inv_h2, op, inv1);
             }
         }
         // second stage: q2 on rows r0 - 1 + j, the output on rows r0 + i
@@ -652,8 +493,9 @@ __device__ __forceinline__ void lim2_strips(const Inst& I, const double* __restr
             const double xl1 = wave_shift<DPP_WAVE_SHR1>(o1[j + 1][VX - 1]), xr1 = wave_shift<DPP_WAVE_SHL1>(o1[j + 1][0]);
 #pragma unroll
             for (int e = 0; e < VX; ++e)
-                q2[j][e] = dcoef(y[j + 2][e], eyre) * o1[j + 1][e] +
-                           e2ih2 * lap5<double, VX>(o1[j], o1[j + 1], o1[j + 2], xl1, xr1, e) - ccoef(y[j + 2][e], eyre);
+                q2[j][e] = lim_inner(dcoef(y[j + 2][e], eyre), o1[j + 1][e], e2ih2,
+                                     lap5<double, VX>(o1[j], o1[j + 1], o1[j + 2], xl1, xr1, e),
+                                     ccoef(y[j + 2][e], eyre));
         }
 #pragma unroll
         for (int i = 0; i < R; ++i) {
@@ -662,9 +504,9 @@ __device__ __forceinline__ void lim2_strips(const Inst& I, const double* __restr
             double o[VX];
 #pragma unroll
             for (int e = 0; e < VX; ++e) {
-                const double r = -inv_h2 * outer_op<MOB, double, VX>(q2[i], q2[i + 1], q2[i + 2], xl1, xr1, mb.row(i + 2),
-                                                                    mb.row(i + 3), mb.row(i + 4), ml, mr, e);
-                o[e] = (y[i + 3][e] + ta2 * o1[i + 2][e] + tau * r) * inv2;
+                const double op = lim_outer<MOB, VX>(q2[i], q2[i + 1], q2[i + 2], xl1, xr1, mb.row(i + 2), mb.row(i + 3),
+                                                     mb.row(i + 4), ml, mr, e);
+                o[e] = lim_next(y[i + 3][e], ta2, o1[i + 2][e], tau, inv_h2, op, inv2);
             }
             if (out && r0 + i < n) store_row<double, VX>(row_rsrc(O + (size_t)(r0 + i) * n, rb), bo, o);
         }

@@ -1,0 +1,125 @@
+"""Launches whose workgroups exchange data while they run, against the ordinary
+launches of the same step.
+
+Both form every point with the same expressions, so they agree bit for bit.
+The ordinary launches are forced with a wait bound of zero
+(CH_RESIDENT_WAIT_US, read when a context is created): the workgroups give up
+at their first wait, exit, and the host repeats the step.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from oracle import ch_oracle as O
+from paper_2502_14589_amd import ch
+from paper_2502_14589_amd.inputs import uniform_field
+
+
+def say(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+def dev(y):
+    import torch
+
+    return torch.from_numpy(np.ascontiguousarray(y, dtype=np.float64)).to("cuda")
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = ch.Context(0)
+    yield c
+    c.close()
+
+
+@pytest.fixture(scope="module")
+def plain():
+    """A context whose resident launches give up at once."""
+    mp = pytest.MonkeyPatch()
+    mp.setenv("CH_RESIDENT_WAIT_US", "0")
+    c = ch.Context(0)
+    mp.undo()
+    yield c
+    c.close()
+
+
+def rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+# one tile, tiles of the least size, one and two tiles per row, odd sides, many tiles
+@pytest.mark.parametrize("n", [5, 13, 64, 97, 121, 250])
+@pytest.mark.parametrize("kind", ["periodic", "neumann", "mobility", "eyre"])
+def test_lim_stages(ctx, plain, n, kind):
+    say(f"resident LIM n={n} {kind}")
+    length = 64.0 if kind == "neumann" else 1.0
+    h = length / n
+    kw = {"eyre": kind == "eyre", "length": length}
+    if kind == "mobility":
+        kw["mobility"] = (0.1, 1.0)
+    bc = ch.CH_BC_NEUMANN if kind == "neumann" else ch.CH_BC_PERIODIC
+    p = ch.Problem(2, n, 3.0 * h, bc=bc, **kw)
+    y0 = uniform_field(n, 2, 0.1, 0.4, seed=8100 + n)
+    tau = 40.0 * h ** 4 / p.eps ** 2
+    out = []
+    for c in (ctx, plain):
+        y = dev(y0)
+        st, recs = c.run_lim(p, y, tau, max_steps=3, records=True)
+        out.append((y.cpu().numpy(), st, recs))
+    assert out[0][1:] == out[1][1:] and st["steps"] == 3 and recs[0]["j"] >= 10
+    assert np.array_equal(out[0][0], out[1][0])
+    if n <= 97:
+        okw = {"eyre": kind == "eyre", "length": length, "mobility": kw.get("mobility")}
+        po = O.Problem(2, n, 3.0 * h, bc="neumann" if kind == "neumann" else "periodic", **okw)
+        y_ref, _ = O.lim_const_run(y0, po, tau, 3)
+        assert rel(out[0][0], y_ref) <= 1e-10
+
+
+def test_lim_run_to_a_final_time(ctx, plain):
+    """The end of a run found on the device: adaptive steps until T, more than are issued between two looks."""
+    n = 72
+    p = ch.Problem(2, n, 0.04)
+    y0 = uniform_field(n, 2, 0.1, 0.05, seed=8200)
+    out = []
+    for c in (ctx, plain):
+        y = dev(y0)
+        st, _ = c.run_lim(p, y, 1e-6, T=4e-4, tol=1e-4)
+        out.append((y.cpu().numpy(), st))
+    assert out[0][1] == out[1][1] and st["t"] == 4e-4 and st["steps"] > 32
+    assert np.array_equal(out[0][0], out[1][0])
+
+
+def test_two_threads_share_the_device():
+    """Two contexts in two threads at sizes that together exceed the device's CUs: one of them takes the ordinary
+    launches, both give the result of a run alone."""
+    import threading
+
+    n = 640
+    p = ch.Problem(2, n, 0.01)
+    y0 = uniform_field(n, 2, 0.1, 0.4, seed=8300)
+    tau = 400.0 / n ** 4 / p.eps ** 2
+    with ch.Context(0) as c:
+        y = dev(y0)
+        c.run_lim(p, y, tau, max_steps=4)
+        ref = y.cpu().numpy()
+    got = [None] * 3
+
+    def work(i):
+        with ch.Context(0) as c:
+            y = dev(y0)
+            for _ in range(5):
+                y.copy_(dev(y0))
+                c.run_lim(p, y, tau, max_steps=4)
+            got[i] = y.cpu().numpy()
+
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(3)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for g in got:
+        assert np.array_equal(g, ref)
