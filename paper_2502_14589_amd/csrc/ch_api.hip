@@ -42,6 +42,8 @@ struct ch_ctx {
     int slots = 0;           // control blocks allocated
     size_t rec_n = 0;        // step records allocated
     int cus = 0;             // compute units of the device
+    int epoch = 0;           // last flag value given to a resident launch
+    CycleShape cyc{0, 0};    // resident Krylov cycles of the current call (waves = 0: ordinary launches)
     int phibig_slots = 0;    // slots of the phi scratch of orders above 48
     ch_step_record* rec = nullptr;
     std::vector<int> expect; // per slot: Krylov cycles issued (compared with the device's `cyc`)
@@ -290,11 +292,28 @@ public:
 };
 std::atomic<int> ResidentLease::used[ResidentLease::DEVICES];
 
-// The flags of the context's resident launches (cleared on the device before
-// each use).
-int ensure_resident(ch_ctx* ctx) {
+// The words of the context's resident launches and the partials of its
+// resident Krylov cycles.
+int ensure_resident(ch_ctx* ctx, bool cycle) {
+    int rc;
+    if (cycle && !ctx->b.cyc && (rc = alloc_dev(ctx, (void**)&ctx->b.cyc, sizeof(double) * cycle_doubles()))) return rc;
     if (ctx->b.flags) return CH_OK;
-    return alloc_dev(ctx, (void**)&ctx->b.flags, sizeof(int) * CH_RES_WORDS);
+    if ((rc = alloc_dev(ctx, (void**)&ctx->b.flags, sizeof(int) * CH_RES_WORDS))) return rc;
+    HIP_TRY(ctx, hipMemsetAsync(ctx->b.flags, 0, sizeof(int) * CH_RES_WORDS, ctx->stream));
+    ctx->epoch = 1;
+    return CH_OK;
+}
+
+// The epoch of a resident launch that uses `count` values above it (the
+// words start over long before an int overflows).
+int next_epoch(ch_ctx* ctx, int count, int* epoch) {
+    if (ctx->epoch > (1 << 30)) {
+        HIP_TRY(ctx, hipMemsetAsync(ctx->b.flags, 0, sizeof(int) * CH_RES_WORDS, ctx->stream));
+        ctx->epoch = 1;
+    }
+    *epoch = ctx->epoch;
+    ctx->epoch += count;
+    return CH_OK;
 }
 
 struct Member {
@@ -527,6 +546,43 @@ bool all_halted(const ch_ctx* ctx, int n) {
     return true;
 }
 
+// The Arnoldi iterations and phi tests of one cycle: resident (ctx->cyc) or
+// as ordinary launches.
+int issue_cycle(ch_ctx* ctx, const Table& t, int prec, PartSeq& ps, const double* y, int m_max, int orth) {
+    if (ctx->cyc.waves > 0) {
+        int epoch, rc;
+        if ((rc = next_epoch(ctx, CYCLE_EPOCHS, &epoch))) return rc;
+        HIP_TRY(ctx, launch_cycle(t, prec, ctx->b, ctx->cyc, epoch, y, m_max, ctx->stream));
+        return CH_OK;
+    }
+    HIP_TRY(ctx, launch_arnoldi(t, prec, ctx->b, ps, y, m_max, orth, ctx->expect.data(), &ctx->env, ctx->stream));
+    return CH_OK;
+}
+
+// Decides whether the cycles of a call on a single grid are resident.  The
+// lease is held until the call returns.
+void use_resident_cycles(ch_ctx* ctx, const Table& t, int m_max, int orth, int graph_chunk, ResidentLease* lease) {
+    ctx->cyc = CycleShape{0, 0};
+    if (orth != CH_ORTH_DCGS2 || graph_chunk > 0) return;
+    const CycleShape c = cycle_shape(t, m_max, ctx->cus);
+    if (c.waves > 0 && ensure_resident(ctx, true) == CH_OK && lease->take(ctx->device, ctx->cus, c.workgroups)) ctx->cyc = c;
+}
+
+// After read_heads: true when a resident cycle gave up waiting.  The run then
+// goes on from the last accepted state with ordinary launches.
+bool resident_retry(ch_ctx* ctx, int* rc) {
+    Ctl& h = ctx->hctl[0];
+    *rc = CH_OK;
+    if (h.status != CH_RES_RETRY) return false;
+    ctx->cyc = CycleShape{0, 0};
+    h.status = CH_OK;
+    h.halted = 0;
+    h.restarts -= h.cycles - 1;   // those of the unfinished step, which begins again
+    ctx->expect[0] = h.cyc;
+    if (hipMemcpyAsync(ctx->b.ctl, &h, CTL_HEAD, hipMemcpyHostToDevice, ctx->stream) != hipSuccess) *rc = CH_EDEVICE;
+    return true;
+}
+
 // Remaining Krylov cycles of a constant step of one instance (linear RT
 // restarts, reading in the oracle's header): re-start from the current
 // sub-step state `z` with the residual of the frozen problem, until a cycle
@@ -543,7 +599,7 @@ int restart_cycles(ch_ctx* ctx, const Table& t, int prec, PartSeq& ps, const dou
         ctx->expect[t.hinst[0].slot] += 1;
         HIP_TRY(ctx, launch_resid(t, prec, b, ps, y, z, false, false, ctx->stream));
         HIP_TRY(ctx, launch_after_resid(t, b, ps, false, ctx->stream));
-        HIP_TRY(ctx, launch_arnoldi(t, prec, b, ps, y, m_max, orth, ctx->expect.data(), &ctx->env, ctx->stream));
+        if ((rc = issue_cycle(ctx, t, prec, ps, y, m_max, orth))) return rc;
         HIP_TRY(ctx, launch_update(t, prec, b, z, z, orth == CH_ORTH_DCGS2, ctx->stream));
     }
     ctx->err = "restart cycle limit reached";
@@ -562,21 +618,23 @@ void fill_stats(const Ctl& h, ch_run_stats* st) {
 }
 
 // Issue EE2 steps for every instance of the table until all are halted (each
-// stops at its own T or step limit) or `max_launch` steps have been issued.
+// stops at its own T or step limit) or `max_launch` steps have been issued,
+// the first `done` of them before this call.
 bool graph_chunk_ok(const ch_ee_opts* o) { return o->graph_chunk >= 0 && o->graph_chunk <= CH_MMAX + 1; }
 
-int issue_ee_steps(ch_ctx* ctx, const Table& t, int prec, int m_max, int orth, bool constant, long long max_launch) {
+int issue_ee_steps(ch_ctx* ctx, const Table& t, int prec, int m_max, int orth, bool constant, long long max_launch,
+                   long long done = 0) {
     const DevBuffers& b = ctx->b;
     PartSeq ps;
     ps.base = b.part;
     int rc;
-    HIP_TRY(ctx, launch_resid(t, prec, b, ps, b.ybuf[0], b.ybuf[0], true, true, ctx->stream));
+    const double* y0 = b.ybuf[done & 1];
+    HIP_TRY(ctx, launch_resid(t, prec, b, ps, y0, y0, true, true, ctx->stream));
     HIP_TRY(ctx, launch_after_resid(t, b, ps, true, ctx->stream));
     for (int i = 0; i < t.ninst; ++i) ctx->expect[t.hinst[i].slot] += 1;
-    for (long long s = 0; s < max_launch; ++s) {
+    for (long long s = done; s < max_launch; ++s) {
         const int p = (int)(s & 1);
-        HIP_TRY(ctx, launch_arnoldi(t, prec, b, ps, b.ybuf[p], m_max, orth, ctx->expect.data(), &ctx->env,
-                                    ctx->stream));
+        if ((rc = issue_cycle(ctx, t, prec, ps, b.ybuf[p], m_max, orth))) return rc;
         HIP_TRY(ctx, launch_update(t, prec, b, b.ybuf[p], b.ybuf[p ^ 1], orth == CH_ORTH_DCGS2, ctx->stream));
         if (constant && (rc = restart_cycles(ctx, t, prec, ps, b.ybuf[p], b.ybuf[p ^ 1], m_max, orth))) return rc;
         HIP_TRY(ctx, launch_est_ee(t, prec, b, ps, b.ybuf[p], b.ybuf[p ^ 1], ctx->stream));
@@ -627,11 +685,19 @@ int run_ee(ch_ctx* ctx, const ch_problem* prob, double* y, double tau0, double t
     HIP_TRY(ctx, hipMemcpyAsync(ctx->b.ctl, ctx->hctl, sizeof(Ctl), hipMemcpyHostToDevice, ctx->stream));
     if ((rc = copy_in(ctx, m, y))) return rc;
     const long long limit = max_steps > 0 ? max_steps : (1LL << 40);
-    ctx->env.graph_chunk = opts->graph_chunk;
-    rc = issue_ee_steps(ctx, t, prec, opts->m_max, opts->orth, constant, limit);
-    ctx->env.graph_chunk = 0;
-    if (rc) return rc;
-    if ((rc = read_heads(ctx, 1))) return rc;
+    ResidentLease lease;
+    use_resident_cycles(ctx, t, opts->m_max, opts->orth, opts->graph_chunk, &lease);
+    long long done = 0;
+    for (bool again = true; again;) {
+        ctx->env.graph_chunk = opts->graph_chunk;
+        rc = issue_ee_steps(ctx, t, prec, opts->m_max, opts->orth, constant, limit, done);
+        ctx->env.graph_chunk = 0;
+        if (rc) return rc;
+        if ((rc = read_heads(ctx, 1))) return rc;
+        again = resident_retry(ctx, &rc);
+        if (rc) return rc;
+        done = ctx->hctl[0].steps;
+    }
     if ((rc = copy_out(ctx, m, 0, y))) return rc;
     const Ctl& h = ctx->hctl[0];
     const int nrec = std::min(h.steps, recs);
@@ -676,6 +742,7 @@ int run_ee_batch(ch_ctx* ctx, int count, const ch_batch_item* items, int dim, in
         if ((rc = copy_in(ctx, ms[i], it.y))) return rc;
     }
     HIP_TRY(ctx, hipMemcpyAsync(ctx->b.ctl, ctx->hctl, sizeof(Ctl) * count, hipMemcpyHostToDevice, ctx->stream));
+    ctx->cyc = CycleShape{0, 0};
     ctx->env.graph_chunk = opts->graph_chunk;
     rc = issue_ee_steps(ctx, t, prec, opts->m_max, opts->orth, false, limit);
     ctx->env.graph_chunk = 0;
@@ -787,7 +854,9 @@ int issue_lim_resident(ch_ctx* ctx, const Table& t, const LimTiles& g, PartSeq& 
         double* yout = b.ybuf[(k + 1) & 1];
         HIP_TRY(ctx, launch_lim_begin(t, b, ps, yin, ctx->stream));
         HIP_TRY(ctx, launch_lim_plan(t, b, ps, ++ctx->lseq, ctx->stream));
-        HIP_TRY(ctx, launch_lim_run(t, b, g, yin, yout, ctx->stream));
+        int epoch;
+        if ((rc = next_epoch(ctx, LIM_EPOCHS, &epoch))) return rc;
+        HIP_TRY(ctx, launch_lim_run(t, b, g, epoch, yin, yout, ctx->stream));
         HIP_TRY(ctx, launch_est_lim(t, b, ps, yin, yout, ctx->stream));
         HIP_TRY(ctx, launch_lim_end(t, b, ps, ctx->stream));
     }
@@ -826,7 +895,7 @@ int run_lim(ch_ctx* ctx, const ch_problem* prob, double* y, double tau0, double 
     ResidentLease lease;   // held until the call returns: its stream has drained then
     if (uses_strips(t)) {
         const LimTiles g = lim_tiles(t.hinst[0], ctx->cus);
-        if (g.rows > 0 && ensure_resident(ctx) == CH_OK && lease.take(ctx->device, ctx->cus, g.ntx * g.nty)) {
+        if (g.rows > 0 && ensure_resident(ctx, false) == CH_OK && lease.take(ctx->device, ctx->cus, g.ntx * g.nty)) {
             if ((rc = issue_lim_resident(ctx, t, g, ps, max_steps, &s0, &done))) return rc;
         }
     }
@@ -1323,7 +1392,7 @@ int ch_destroy(ch_ctx* ctx) {
     destroy_graphs(ctx->graphs);
     for (void* p : {(void*)b.V, (void*)b.ybuf[0], (void*)b.ybuf[1], (void*)b.fcur, (void*)b.y32, (void*)b.zbuf,
                     (void*)b.part, (void*)b.dots, (void*)b.lorder, (void*)b.ctl, (void*)ctx->rec, b.phibig,
-                    (void*)b.lcoef, (void*)b.dcount, (void*)b.flags})
+                    (void*)b.lcoef, (void*)b.dcount, (void*)b.flags, (void*)b.cyc})
         free_dev(p);
     for (auto& ts : ctx->store)
         for (void* p : {(void*)ts.d_inst, (void*)ts.d_sb2i, (void*)ts.d_cb2i, (void*)ts.d_wb2i}) free_dev(p);
@@ -1487,15 +1556,21 @@ int ch_phiv(ch_ctx* ctx, const ch_problem* prob, const double* y, double* y_out,
     if ((rc = copy_in(ctx, m, y))) return rc;
     PartSeq ps;
     ps.base = b.part;
-    HIP_TRY(ctx, launch_resid(t, prec, b, ps, b.ybuf[0], b.ybuf[0], false, true, ctx->stream));
-    HIP_TRY(ctx, launch_after_resid(t, b, ps, true, ctx->stream));
-    ctx->expect[0] += 1;
-    HIP_TRY(ctx, launch_arnoldi(t, prec, b, ps, b.ybuf[0], m_max, CH_ORTH_DCGS2, ctx->expect.data(), &ctx->env,
-                                ctx->stream));
-    HIP_TRY(ctx, launch_update(t, prec, b, b.ybuf[0], b.ybuf[1], true, ctx->stream));
-    if (mode == CH_PHI_RESTART && (rc = restart_cycles(ctx, t, prec, ps, b.ybuf[0], b.ybuf[1], m_max, CH_ORTH_DCGS2)))
-        return rc;
-    if ((rc = read_heads(ctx, 1))) return rc;
+    ResidentLease lease;
+    use_resident_cycles(ctx, t, m_max, CH_ORTH_DCGS2, 0, &lease);
+    for (bool again = true; again;) {
+        HIP_TRY(ctx, launch_resid(t, prec, b, ps, b.ybuf[0], b.ybuf[0], false, true, ctx->stream));
+        HIP_TRY(ctx, launch_after_resid(t, b, ps, true, ctx->stream));
+        ctx->expect[0] += 1;
+        if ((rc = issue_cycle(ctx, t, prec, ps, b.ybuf[0], m_max, CH_ORTH_DCGS2))) return rc;
+        HIP_TRY(ctx, launch_update(t, prec, b, b.ybuf[0], b.ybuf[1], true, ctx->stream));
+        if (mode == CH_PHI_RESTART &&
+            (rc = restart_cycles(ctx, t, prec, ps, b.ybuf[0], b.ybuf[1], m_max, CH_ORTH_DCGS2)))
+            return rc;
+        if ((rc = read_heads(ctx, 1))) return rc;
+        again = resident_retry(ctx, &rc);
+        if (rc) return rc;
+    }
     const Ctl& h = ctx->hctl[0];
     if (h.status == CH_OK)
         HIP_TRY(ctx, hipMemcpyAsync(y_out, b.ybuf[1], sizeof(double) * sh.N, hipMemcpyDeviceToDevice, ctx->stream));

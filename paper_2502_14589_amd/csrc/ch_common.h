@@ -85,6 +85,21 @@ __device__ __forceinline__ double wave_sum8(double (&a)[8]) {
 // or -1 (each value is stored by one lane).
 __device__ __forceinline__ int wave_sum8_holder(int lane) { return (lane & 0x31) == 0 ? (lane >> 1) & 7 : -1; }
 
+// x of lane `lane` (wave-uniform), in every lane.
+__device__ __forceinline__ double readlane_d(double x, int lane) {
+    const unsigned long long v = __builtin_bit_cast(unsigned long long, x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, lane);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), lane);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// a b, rounded: not contracted into an addition that uses it, so that kernels
+// that share a formula agree bit for bit.
+__device__ __forceinline__ double product(double a, double b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
+
 enum RedOp { RED_SUM = 0, RED_MIN = 1, RED_MAX = 2 };
 
 template <int OP>

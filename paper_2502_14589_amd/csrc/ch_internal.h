@@ -151,6 +151,7 @@ struct DevBuffers {
     int* dlim;          // device view of `hlim`
     const volatile int* hlim;   // pinned host words, per slot: the LIM plan's order p (0: halted), then its tag
     int* flags;         // flags of the resident launches (ch_resident.h), or null
+    double* cyc;        // partials and totals of a resident Krylov cycle
     unsigned wait_us;   // bound of their waits
     void* phibig;       // per-slot device scratch of the phi of orders above 48 (phi_big_bytes each)
 };

@@ -22,11 +22,15 @@
 
 // Most workgroups of a resident launch (one per CU).
 #define CH_RES_MAX 256
-// Flag words of a context: one per workgroup, a cache line apart, then the
-// failure word.
+// Words of a context that workgroups poll, each in a cache line of its own:
+// one flag per workgroup, the failure word, the word that ends a Krylov cycle.
+// Nothing clears them between launches: a launch owns the values above its
+// `epoch`, up to the next launch's.
 #define CH_RES_LINE 32
-#define CH_RES_FLAGS (CH_RES_MAX * CH_RES_LINE)
-#define CH_RES_WORDS (CH_RES_FLAGS + CH_RES_LINE)
+#define CH_RES_FAIL (CH_RES_MAX * CH_RES_LINE)
+#define CH_RES_DONE (CH_RES_FAIL + CH_RES_LINE)
+#define CH_RES_CHAIN (CH_RES_DONE + CH_RES_LINE)    // CH_MSMALL + 1 words: phi tests that did not end the cycle
+#define CH_RES_WORDS (CH_RES_CHAIN + 2 * CH_RES_LINE)
 // Status a resident launch leaves in the control block (with halted set)
 // when a wait ran out: never returned to a caller.
 #define CH_RES_RETRY 1000
@@ -52,21 +56,22 @@ __device__ __forceinline__ void res_store(double* p, double v) {
 __device__ __forceinline__ void res_drain() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // True when a wait that has polled `spin` times is to end: `wait_us` ran out
-// since its first poll (t0) or another workgroup gave up.  Sets the failure word.
-__device__ __forceinline__ bool res_expired(unsigned spin, long long& t0, int* fail, unsigned wait_us) {
+// since its first poll (t0) or another workgroup gave up.  Sets the failure
+// word to the launch's epoch.
+__device__ __forceinline__ bool res_expired(unsigned spin, long long& t0, int* fail, int epoch, unsigned wait_us) {
     if (spin & 63) return false;
     const long long now = (long long)wall_clock64();   // 100 MHz
     if (spin == 0) t0 = now;
-    if (res_load(fail) == 0 && now - t0 < 100ll * wait_us) return false;
-    res_store(fail, 1);
+    if (res_load(fail) != epoch && now - t0 < 100ll * wait_us) return false;
+    res_store(fail, epoch);
     return true;
 }
 
 // Waits until *flag >= v; false when the wait expired.
-__device__ __forceinline__ bool res_wait(const int* flag, int v, int* fail, unsigned wait_us) {
+__device__ __forceinline__ bool res_wait(const int* flag, int v, int* fail, int epoch, unsigned wait_us) {
     long long t0 = 0;
     for (unsigned spin = 0; res_load(flag) < v; ++spin) {
-        if (res_expired(spin, t0, fail, wait_us)) return false;
+        if (res_expired(spin, t0, fail, epoch, wait_us)) return false;
         __builtin_amdgcn_s_sleep(1);
     }
     return true;
@@ -105,7 +110,21 @@ struct LimTiles {
 };
 LimTiles lim_tiles(const Inst& I, int cus);
 // All 2p - 1 stages of a LIM step of a single 2-D grid in one launch, from
-// y^n (yin) to yout, p and the stage coefficients from the plan launch, which
-// also clears the flags.
-hipError_t launch_lim_run(const Table& t, const DevBuffers& b, const LimTiles& g, const double* yin, double* yout,
-                          hipStream_t s);
+// y^n (yin) to yout, p and the stage coefficients from the plan launch.  Uses
+// LIM_EPOCHS values above `epoch`.
+#define LIM_EPOCHS (2 * CH_PMAX)
+hipError_t launch_lim_run(const Table& t, const DevBuffers& b, const LimTiles& g, int epoch, const double* yin,
+                          double* yout, hipStream_t s);
+
+// Resident Krylov cycle (ch_cycle.hip) of a single 2-D grid: `waves` per
+// workgroup, workgroups in all; waves = 0: the grid or m_max does not fit.
+struct CycleShape {
+    int waves, workgroups;
+};
+CycleShape cycle_shape(const Table& t, int m_max, int cus);
+size_t cycle_doubles();   // of DevBuffers::cyc
+// All DCGS2 iterations and phi tests of a cycle begun by launch_after_resid or
+// launch_step_end.  Uses CYCLE_EPOCHS values above `epoch`.
+#define CYCLE_EPOCHS 128
+hipError_t launch_cycle(const Table& t, int prec, const DevBuffers& b, const CycleShape& c, int epoch, const double* y,
+                        int m_max, hipStream_t s);

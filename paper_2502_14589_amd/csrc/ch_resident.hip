@@ -38,18 +38,11 @@ constexpr int LIM_WAVES = 8, LIM_ROWS_MAX = 8;
 // First row (column) of tile t of `nt` over n.
 __device__ __forceinline__ int tile_first(int t, int nt, int n) { return (int)((long long)t * n / nt); }
 
-__device__ __forceinline__ double lane_value(double x, int lane) {
-    const unsigned long long v = __builtin_bit_cast(unsigned long long, x);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, lane);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), lane);
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-
 template <int NW, int K, bool MOB>
 __global__ __launch_bounds__(64 * NW, 1) void k_lim_run(Ctl* __restrict__ ctls, const Inst I, int ntx, int nty, int S,
                                                         const double* __restrict__ ybase, double* youtbase,
                                                         double* zbufbase, const double* __restrict__ coefs,
-                                                        int* flags, unsigned wait_us) {
+                                                        int* flags, int epoch, unsigned wait_us) {
     const int H = 2 * S;
     __shared__ double2 edge[2][NW][4][64];   // rows 0, 1, K - 2, K - 1 of each wave, two stages in turn
     __shared__ int dead;
@@ -127,7 +120,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_lim_run(Ctl* __restrict__ ctls, 
             cinv = ninv;
             fetch(pos + 64);
         }
-        const double ta = lane_value(cta, pos & 63), inv = lane_value(cinv, pos & 63);
+        const double ta = readlane_d(cta, pos & 63), inv = readlane_d(cinv, pos & 63);
         double2(*E)[4][64] = edge[pos & 1];
         E[wv][0][lane] = double2{z[0][0], z[0][1]};
         E[wv][1][lane] = double2{z[1][0], z[1][1]};
@@ -209,8 +202,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_lim_run(Ctl* __restrict__ ctls, 
         }
         res_drain();
         __syncthreads();
-        if (threadIdx.x == 0) res_store(flags + tile * CH_RES_LINE, g);
-        if (threadIdx.x < 9 && !res_wait(nflag, g, flags + CH_RES_FLAGS, wait_us)) dead = 1;
+        if (threadIdx.x == 0) res_store(flags + tile * CH_RES_LINE, epoch + g);
+        if (threadIdx.x < 9 && !res_wait(nflag, epoch + g, flags + CH_RES_FAIL, epoch, wait_us)) dead = 1;
         __syncthreads();
         if (dead) {   // the host repeats the step: nothing here is kept
             if (threadIdx.x == 0) {
@@ -240,15 +233,15 @@ __global__ __launch_bounds__(64 * NW, 1) void k_lim_run(Ctl* __restrict__ ctls, 
 }
 
 template <int K>
-void launch_lim_run_k(const Table& t, const DevBuffers& b, const LimTiles& g, const double* yin, double* yout,
-                      hipStream_t s) {
+void launch_lim_run_k(const Table& t, const DevBuffers& b, const LimTiles& g, int epoch, const double* yin,
+                      double* yout, hipStream_t s) {
     const dim3 grid(g.ntx * g.nty), block(64 * LIM_WAVES);
     if (mobility(t))
         hipLaunchKernelGGL((k_lim_run<LIM_WAVES, K, true>), grid, block, 0, s, b.ctl, t.hinst[0], g.ntx, g.nty, g.stages,
-                           yin, yout, b.zbuf, b.lcoef, b.flags, b.wait_us);
+                           yin, yout, b.zbuf, b.lcoef, b.flags, epoch, b.wait_us);
     else
         hipLaunchKernelGGL((k_lim_run<LIM_WAVES, K, false>), grid, block, 0, s, b.ctl, t.hinst[0], g.ntx, g.nty, g.stages,
-                           yin, yout, b.zbuf, b.lcoef, b.flags, b.wait_us);
+                           yin, yout, b.zbuf, b.lcoef, b.flags, epoch, b.wait_us);
 }
 
 }  // namespace
@@ -279,16 +272,16 @@ LimTiles lim_tiles(const Inst& I, int cus) {
     return best;
 }
 
-hipError_t launch_lim_run(const Table& t, const DevBuffers& b, const LimTiles& g, const double* yin, double* yout,
-                          hipStream_t s) {
+hipError_t launch_lim_run(const Table& t, const DevBuffers& b, const LimTiles& g, int epoch, const double* yin,
+                          double* yout, hipStream_t s) {
     switch (g.rows) {
-        case 2: launch_lim_run_k<2>(t, b, g, yin, yout, s); break;
-        case 3: launch_lim_run_k<3>(t, b, g, yin, yout, s); break;
-        case 4: launch_lim_run_k<4>(t, b, g, yin, yout, s); break;
-        case 5: launch_lim_run_k<5>(t, b, g, yin, yout, s); break;
-        case 6: launch_lim_run_k<6>(t, b, g, yin, yout, s); break;
-        case 7: launch_lim_run_k<7>(t, b, g, yin, yout, s); break;
-        case 8: launch_lim_run_k<8>(t, b, g, yin, yout, s); break;
+        case 2: launch_lim_run_k<2>(t, b, g, epoch, yin, yout, s); break;
+        case 3: launch_lim_run_k<3>(t, b, g, epoch, yin, yout, s); break;
+        case 4: launch_lim_run_k<4>(t, b, g, epoch, yin, yout, s); break;
+        case 5: launch_lim_run_k<5>(t, b, g, epoch, yin, yout, s); break;
+        case 6: launch_lim_run_k<6>(t, b, g, epoch, yin, yout, s); break;
+        case 7: launch_lim_run_k<7>(t, b, g, epoch, yin, yout, s); break;
+        case 8: launch_lim_run_k<8>(t, b, g, epoch, yin, yout, s); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

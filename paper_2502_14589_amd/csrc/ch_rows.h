@@ -18,20 +18,21 @@ using u32x2 = unsigned __attribute__((ext_vector_type(2)));
 using u32x4 = unsigned __attribute__((ext_vector_type(4)));
 
 // VX consecutive values of type T at byte offset `bo` of row resource r.
-template <typename T, int VX>
+// AUX: the cache-policy bits of the access (16: agent scope, ch_resident.h).
+template <typename T, int VX, int AUX = 0>
 __device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r, unsigned bo, T (&v)[VX]) {
     constexpr unsigned so = 0;
     constexpr int B = VX * (int)sizeof(T);
     if constexpr (B == 4) {
-        v[0] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, bo, so, 0));
+        v[0] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, bo, so, AUX));
     } else if constexpr (B == 8) {
-        const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(r, bo, so, 0);
+        const u32x2 x = __builtin_amdgcn_raw_buffer_load_b64(r, bo, so, AUX);
         struct P { T e[VX]; };
         const P p = __builtin_bit_cast(P, x);
 #pragma unroll
         for (int e = 0; e < VX; ++e) v[e] = p.e[e];
     } else if constexpr (B == 16) {
-        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, bo, so, 0);
+        const u32x4 x = __builtin_amdgcn_raw_buffer_load_b128(r, bo, so, AUX);
         struct P { T e[VX]; };
         const P p = __builtin_bit_cast(P, x);
 #pragma unroll
@@ -40,8 +41,8 @@ __device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r, unsigned bo, 
         static_assert(B == 32, "row chunk of 4, 8, 16 or 32 bytes");
         constexpr int H = VX / 2;
         T a[H], c[H];
-        load_row<T, H>(r, bo, a);
-        load_row<T, H>(r, bo + 16u, c);
+        load_row<T, H, AUX>(r, bo, a);
+        load_row<T, H, AUX>(r, bo + 16u, c);
 #pragma unroll
         for (int e = 0; e < H; ++e) {
             v[e] = a[e];
@@ -50,7 +51,7 @@ __device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r, unsigned bo, 
     }
 }
 
-template <typename T, int VX>
+template <typename T, int VX, int AUX = 0>
 __device__ __forceinline__ void store_row(__amdgpu_buffer_rsrc_t r, unsigned bo, const T (&v)[VX]) {
     constexpr unsigned so = 0;
     constexpr int B = VX * (int)sizeof(T);
@@ -59,11 +60,11 @@ __device__ __forceinline__ void store_row(__amdgpu_buffer_rsrc_t r, unsigned bo,
 #pragma unroll
     for (int e = 0; e < VX; ++e) p.e[e] = v[e];
     if constexpr (B == 4) {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, p), r, bo, so, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, p), r, bo, so, AUX);
     } else if constexpr (B == 8) {
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, p), r, bo, so, 0);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, p), r, bo, so, AUX);
     } else if constexpr (B == 16) {
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, p), r, bo, so, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, p), r, bo, so, AUX);
     } else {
         static_assert(B == 32, "row chunk of 4, 8, 16 or 32 bytes");
         constexpr int H = VX / 2;
@@ -73,8 +74,8 @@ __device__ __forceinline__ void store_row(__amdgpu_buffer_rsrc_t r, unsigned bo,
             a[e] = v[e];
             c[e] = v[H + e];
         }
-        store_row<T, H>(r, bo, a);
-        store_row<T, H>(r, bo + 16u, c);
+        store_row<T, H, AUX>(r, bo, a);
+        store_row<T, H, AUX>(r, bo + 16u, c);
     }
 }
 
@@ -166,6 +167,70 @@ __device__ __forceinline__ T ccoef(T y, int eyre) {
     return T(2) * y * y * y + (eyre ? y : T(0));
 }
 
+constexpr int SR = CH_STRIP_ROWS;
+
+// Strip geometry of one wave.
+template <int VX>
+struct StripPos {
+    int r0;         // first row
+    int xl;         // lane's first column, in [0, n)
+    bool out;       // the lane's columns are outputs of this strip
+    bool need;      // ... or the halo of one
+    bool rev;       // the lane's values are those of its columns in reverse (Neumann mirror)
+};
+
+// Grid column of the first of the VX columns [c, c + VX) of a lane (c a
+// multiple of VX, VX dividing n, -n < c < 2n): periodic wrap, or, past a
+// Neumann boundary, the mirror chunk [-c - VX, -c) or [2n - c - VX, 2n - c),
+// whose values the lane then takes in reverse order (rev).
+template <int VX>
+__device__ __forceinline__ int chunk_col(int c, int n, int bc, bool& rev) {
+    rev = false;
+    if (bc == CH_BC_NEUMANN && (c < 0 || c >= n)) {
+        rev = VX > 1;
+        const int x = c < 0 ? -c - VX : 2 * n - c - VX;
+        return x < 0 ? 0 : x;   // lanes past the halo (never read) stay in bounds
+    }
+    const int x = c % n;
+    return x < 0 ? x + n : x;
+}
+
+// Reverse the VX values of a lane when `rev`, without a branch.
+template <typename T, int VX>
+__device__ __forceinline__ void flip_if(bool rev, T (&v)[VX]) {
+    if constexpr (VX > 1) {
+        T t[VX];
+#pragma unroll
+        for (int e = 0; e < VX; ++e) t[e] = v[VX - 1 - e];
+#pragma unroll
+        for (int e = 0; e < VX; ++e) v[e] = rev ? t[e] : v[e];
+    }
+}
+
+// A lane offset past every row: the load returns zeros without a memory
+// access (lanes that neither own nor border an output column).
+constexpr unsigned OFF_ROW = 0x80000000u;
+
+template <int VX>
+__device__ __forceinline__ StripPos<VX> strip_pos(int s, int nsx, int n, int lane, int bc) {
+    constexpr int HL = CH_STRIP_HALO(VX), OW = strip_cols(VX);
+    StripPos<VX> p;
+    const int sx = s % nsx;
+    p.r0 = (s / nsx) * SR;
+    const int c = sx * OW + (lane - HL) * VX;     // first column, before the boundary fold
+    p.xl = chunk_col<VX>(c, n, bc, p.rev);
+    p.out = lane >= HL && lane < 64 - HL && c < n;
+    p.need = c < n + HL * VX;
+    return p;
+}
+
+// Row r (r in [-n, 2n): periodic wrap or Neumann mirror) of an instance's
+// field of n x n values of type T.
+template <typename T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t grid_row(const T* f, int r, int n, int bc) {
+    return row_rsrc(f + (size_t)bc_index(r, n, bc) * n, (unsigned)n * (unsigned)sizeof(T));
+}
+
 // ---------------------------------------------------------------------------
 // Arithmetic of one LIM stage at one point (Fig. 1).  Which products are fused
 // into sums is written out, and the stage's result is rounded, so that every
@@ -200,6 +265,71 @@ __device__ __forceinline__ double lim_outer(const double (&up)[VX], const double
         return 0.5 * (fx + fy);
     } else {
         return __builtin_fma(4.0, c[e], -((l + r) + (up[e] + dn[e])));
+    }
+}
+
+__device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// w = Ahat (sc u) on a strip's rows r0 .. r0 + SR - 1 from the operand's rows
+// r0 - 2 .. (scaled in place) and the state's rows r0 - 1 ...  Which products are fused
+// into sums is written out, so that every kernel that forms a matvec gives the
+// same bits: of two neighbours the outer row's, or the one nearer the lane's
+// middle, enters unscaled with its scaling fused.
+template <typename TV, int VX, bool MOB>
+__device__ __forceinline__ void matvec_rows(TV (&u)[SR + 4][VX], const TV (&y)[SR + 2][VX], TV sc, int eyre, TV ih2,
+                                            TV e2ih2, Mob mob, TV (&w)[SR][VX]) {
+#pragma clang fp contract(off)
+    constexpr int NU = SR + 4, ND = SR + 2;
+    TV raw[NU][VX];
+#pragma unroll
+    for (int j = 0; j < NU; ++j)
+#pragma unroll
+        for (int e = 0; e < VX; ++e) {
+            raw[j][e] = u[j][e];
+            u[j][e] *= sc;
+        }
+    MobRows<MOB, TV, VX, ND> mb;
+#pragma unroll
+    for (int j = 0; j < ND; ++j) mb.set(j, y[j], TV(mob.m0), TV(mob.m1));
+    // inner expression d u + eps^2 A u on rows r0 - 1 .. r0 + SR
+    TV q[ND][VX];
+#pragma unroll
+    for (int j = 0; j < ND; ++j) {
+        const TV xl = wave_shift<DPP_WAVE_SHR1>(u[j + 1][VX - 1]), xr = wave_shift<DPP_WAVE_SHL1>(u[j + 1][0]);
+#pragma unroll
+        for (int e = 0; e < VX; ++e) {
+            const TV l = e > 0 ? u[j + 1][e - 1] : xl, r = e < VX - 1 ? u[j + 1][e + 1] : xr;
+            TV nx;
+            if (VX == 1) nx = l + r;
+            else if (2 * e < VX) nx = fma_of(sc, raw[j + 1][e < VX - 1 ? e + 1 : e], l);
+            else nx = fma_of(sc, raw[j + 1][e > 0 ? e - 1 : e], r);
+            const TV ny = 2 * j < ND ? fma_of(sc, raw[j][e], u[j + 2][e]) : fma_of(sc, raw[j + 2][e], u[j][e]);
+            const TV lap = fma_of(TV(4), u[j + 1][e], -(nx + ny));
+            const TV d = fma_of(y[j][e], TV(3) * y[j][e], TV(-1)) + TV(eyre);
+            if (VX == 4 && (e == 1 || e == 2)) q[j][e] = fma_of(lap, e2ih2, d * u[j + 1][e]);
+            else q[j][e] = fma_of(d, u[j + 1][e], lap * e2ih2);
+        }
+    }
+    // w = A q (A_M q with mobility) on rows r0 .. r0 + SR - 1
+#pragma unroll
+    for (int i = 0; i < SR; ++i) {
+        const TV xl = wave_shift<DPP_WAVE_SHR1>(q[i + 1][VX - 1]), xr = wave_shift<DPP_WAVE_SHL1>(q[i + 1][0]);
+        const TV ml = mb.left(i + 1), mr = mb.right(i + 1);
+#pragma unroll
+        for (int e = 0; e < VX; ++e) {
+            const TV c = q[i + 1][e];
+            const TV l = e > 0 ? q[i + 1][e - 1] : xl, r = e < VX - 1 ? q[i + 1][e + 1] : xr;
+            if constexpr (MOB) {
+                const TV m = mb.row(i + 1)[e];
+                const TV a = m + (e > 0 ? mb.row(i + 1)[e - 1] : ml), b = m + (e < VX - 1 ? mb.row(i + 1)[e + 1] : mr);
+                const TV fx = 2 * e + 1 < VX ? fma_of(b, c - r, a * (c - l)) : fma_of(a, c - l, b * (c - r));
+                const TV fy = fma_of(m + mb.row(i)[e], c - q[i][e], (m + mb.row(i + 2)[e]) * (c - q[i + 2][e]));
+                w[i][e] = ih2 * (TV(0.5) * (fx + fy));
+            } else {
+                w[i][e] = ih2 * fma_of(TV(4), c, -((l + r) + (q[i][e] + q[i + 2][e])));
+            }
+        }
     }
 }
 

@@ -23,70 +23,6 @@
 
 namespace {
 
-constexpr int SR = CH_STRIP_ROWS;
-
-// Strip geometry of one wave.
-template <int VX>
-struct StripPos {
-    int r0;         // first row
-    int xl;         // lane's first column, in [0, n)
-    bool out;       // the lane's columns are outputs of this strip
-    bool need;      // ... or the halo of one
-    bool rev;       // the lane's values are those of its columns in reverse (Neumann mirror)
-};
-
-// Grid column of the first of the VX columns [c, c + VX) of a lane (c a
-// multiple of VX, VX dividing n, -n < c < 2n): periodic wrap, or, past a
-// Neumann boundary, the mirror chunk [-c - VX, -c) or [2n - c - VX, 2n - c),
-// whose values the lane then takes in reverse order (rev).
-template <int VX>
-__device__ __forceinline__ int chunk_col(int c, int n, int bc, bool& rev) {
-    rev = false;
-    if (bc == CH_BC_NEUMANN && (c < 0 || c >= n)) {
-        rev = VX > 1;
-        const int x = c < 0 ? -c - VX : 2 * n - c - VX;
-        return x < 0 ? 0 : x;   // lanes past the halo (never read) stay in bounds
-    }
-    const int x = c % n;
-    return x < 0 ? x + n : x;
-}
-
-// Reverse the VX values of a lane when `rev`, without a branch.
-template <typename T, int VX>
-__device__ __forceinline__ void flip_if(bool rev, T (&v)[VX]) {
-    if constexpr (VX > 1) {
-        T t[VX];
-#pragma unroll
-        for (int e = 0; e < VX; ++e) t[e] = v[VX - 1 - e];
-#pragma unroll
-        for (int e = 0; e < VX; ++e) v[e] = rev ? t[e] : v[e];
-    }
-}
-
-// A lane offset past every row: the load returns zeros without a memory
-// access (lanes that neither own nor border an output column).
-constexpr unsigned OFF_ROW = 0x80000000u;
-
-template <int VX>
-__device__ __forceinline__ StripPos<VX> strip_pos(int s, int nsx, int n, int lane, int bc) {
-    constexpr int HL = CH_STRIP_HALO(VX), OW = strip_cols(VX);
-    StripPos<VX> p;
-    const int sx = s % nsx;
-    p.r0 = (s / nsx) * SR;
-    const int c = sx * OW + (lane - HL) * VX;     // first column, before the boundary fold
-    p.xl = chunk_col<VX>(c, n, bc, p.rev);
-    p.out = lane >= HL && lane < 64 - HL && c < n;
-    p.need = c < n + HL * VX;
-    return p;
-}
-
-// Row r (r in [-n, 2n): periodic wrap or Neumann mirror) of an instance's
-// field of n x n values of type T.
-template <typename T>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t grid_row(const T* f, int r, int n, int bc) {
-    return row_rsrc(f + (size_t)bc_index(r, n, bc) * n, (unsigned)n * (unsigned)sizeof(T));
-}
-
 // ---------------------------------------------------------------------------
 // w = Ahat u, u = vscale[k] V_k (the matvec of Fig. 3), stored in column k + 1
 // (unless store_w is 0), with the partials of its dot products:
@@ -139,37 +75,8 @@ __device__ __forceinline__ double matvec_strips(const Inst& I, const MatvecArgs<
         for (int j = 0; j < NU; ++j) flip_if<TV, VX>(P.rev, u[j]);
 #pragma unroll
         for (int j = 0; j < ND; ++j) flip_if<TV, VX>(P.rev, d[j]);
-#pragma unroll
-        for (int j = 0; j < NU; ++j)
-#pragma unroll
-            for (int e = 0; e < VX; ++e) u[j][e] *= sc;
-        MobRows<MOB, TV, VX, ND> mb;
-#pragma unroll
-        for (int j = 0; j < ND; ++j) mb.set(j, d[j], TV(mob.m0), TV(mob.m1));
-#pragma unroll
-        for (int j = 0; j < ND; ++j)
-#pragma unroll
-            for (int e = 0; e < VX; ++e) d[j][e] = dcoef(d[j][e], eyre);
-        // inner expression d u + eps^2 A u on rows r0 - 1 .. r0 + SR
-        TV q[ND][VX];
-#pragma unroll
-        for (int j = 0; j < ND; ++j) {
-            const TV xl = wave_shift<DPP_WAVE_SHR1>(u[j + 1][VX - 1]), xr = wave_shift<DPP_WAVE_SHL1>(u[j + 1][0]);
-#pragma unroll
-            for (int e = 0; e < VX; ++e)
-                q[j][e] = d[j][e] * u[j + 1][e] + e2ih2 * lap5<TV, VX>(u[j], u[j + 1], u[j + 2], xl, xr, e);
-        }
-        // w = A q (A_M q with mobility) on rows r0 .. r0 + SR - 1
         TV w[SR][VX];
-#pragma unroll
-        for (int i = 0; i < SR; ++i) {
-            const TV xl = wave_shift<DPP_WAVE_SHR1>(q[i + 1][VX - 1]), xr = wave_shift<DPP_WAVE_SHL1>(q[i + 1][0]);
-            const TV ml = mb.left(i + 1), mr = mb.right(i + 1);
-#pragma unroll
-            for (int e = 0; e < VX; ++e)
-                w[i][e] = ih2 * outer_op<MOB, TV, VX>(q[i], q[i + 1], q[i + 2], xl, xr, mb.row(i), mb.row(i + 1),
-                                                      mb.row(i + 2), ml, mr, e);
-        }
+        matvec_rows<TV, VX, MOB>(u, d, sc, eyre, ih2, e2ih2, mob, w);
         bool rowin[SR];
 #pragma unroll
         for (int i = 0; i < SR; ++i) rowin[i] = P.r0 + i < n;
@@ -223,8 +130,8 @@ __device__ __forceinline__ double matvec_strips(const Inst& I, const MatvecArgs<
 #pragma unroll
                         for (int e = 0; e < VX; ++e) {
                             const double qv = double(bl[r][i][e]);
-                            su += ud[i][e] * qv;
-                            sw += wd[i][e] * qv;
+                            su = __builtin_fma(ud[i][e], qv, su);
+                            sw = __builtin_fma(wd[i][e], qv, sw);
                         }
                     a[2 * r] = su;
                     a[2 * r + 1] = sw;
@@ -247,8 +154,8 @@ __device__ __forceinline__ double matvec_strips(const Inst& I, const MatvecArgs<
             for (int i = 0; i < SR; ++i)
 #pragma unroll
                 for (int e = 0; e < VX; ++e) {
-                    b8[0] += ud[i][e] * ud[i][e];
-                    b8[1] += ud[i][e] * wd[i][e];
+                    b8[0] = __builtin_fma(ud[i][e], ud[i][e], b8[0]);
+                    b8[1] = __builtin_fma(ud[i][e], wd[i][e], b8[1]);
                 }
             const double tot = wave_sum8(b8);
             if (hv == 0 || hv == 1) red[2 * k + hv][wv] += tot;

@@ -93,9 +93,48 @@ def test_lim_run_to_a_final_time(ctx, plain):
     assert np.array_equal(out[0][0], out[1][0])
 
 
+# one group; widths of 1, 2 and 4 columns per lane; a last strip of one column (FP64 strips are 124 wide, FP32 248);
+# four, eight and twelve waves per workgroup (512 and 760 in FP64)
+@pytest.mark.parametrize("prec", [ch.CH_FP64, ch.CH_FP32_MIXED])
+@pytest.mark.parametrize("n,kind", [(5, "periodic"), (63, "periodic"), (64, "neumann"), (66, "mobility"), (125, "periodic"),
+                                    (125, "neumann"), (249, "mobility"), (250, "neumann"), (512, "periodic"), (760, "periodic")])
+def test_krylov_cycles(ctx, plain, n, kind, prec):
+    """Adaptive steps (the first shortened by the trace, later ones converging early) and restarted cycles of a constant
+    step: field, records and statistics equal those of the ordinary launches."""
+    say(f"resident cycles n={n} {kind} prec={prec}")
+    length = 64.0 if kind == "neumann" else 1.0
+    h = length / n
+    bc = ch.CH_BC_NEUMANN if kind == "neumann" else ch.CH_BC_PERIODIC
+    p = ch.Problem(2, n, 3.0 * h, precision=prec, bc=bc, length=length, mobility=(0.1, 1.0) if kind == "mobility" else None)
+    y0 = uniform_field(n, 2, 0.1, 0.4, seed=8400 + n)
+    rho = p.eps ** 2 * 64.0 / h ** 4
+    out = []
+    for c in (ctx, plain):
+        y = dev(y0)
+        st, recs = c.run_ee(p, y, 400.0 / rho, max_steps=3, m_max=30, records=True)
+        z = dev(y0)
+        st2, recs2 = c.run_ee(p, z, 60.0 / rho, max_steps=2, m_max=8, tol_phi_fixed=1e-6, constant_step=True, records=True)
+        out.append((y.cpu().numpy(), z.cpu().numpy(), st, recs, st2, recs2))
+    assert out[0][2:] == out[1][2:] and st["steps"] == 3 and st2["steps"] == 2
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+def test_phiv_cycles(ctx, plain):
+    n = 96
+    p = ch.Problem(2, n, 0.03)
+    y0 = uniform_field(n, 2, 0.1, 0.4, seed=8500)
+    out = []
+    for c in (ctx, plain):
+        y, z = dev(y0), dev(y0)
+        rec = c.phiv(p, y, z, 2e-5, mode=ch.CH_PHI_RESTART, m_max=12)
+        out.append((z.cpu().numpy(), rec))
+    assert out[0][1] == out[1][1] and rec["cycles"] > 1
+    assert np.array_equal(out[0][0], out[1][0])
+
+
 def test_two_threads_share_the_device():
-    """Two contexts in two threads at sizes that together exceed the device's CUs: one of them takes the ordinary
-    launches, both give the result of a run alone."""
+    """Three contexts in three threads at sizes that together exceed the device's CUs: some take the ordinary
+    launches, all give the result of a run alone."""
     import threading
 
     n = 640
@@ -105,6 +144,7 @@ def test_two_threads_share_the_device():
     with ch.Context(0) as c:
         y = dev(y0)
         c.run_lim(p, y, tau, max_steps=4)
+        c.run_ee(p, y, 1e-9, max_steps=3)
         ref = y.cpu().numpy()
     got = [None] * 3
 
@@ -114,6 +154,7 @@ def test_two_threads_share_the_device():
             for _ in range(5):
                 y.copy_(dev(y0))
                 c.run_lim(p, y, tau, max_steps=4)
+                c.run_ee(p, y, 1e-9, max_steps=3)
             got[i] = y.cpu().numpy()
 
     ts = [threading.Thread(target=work, args=(i,)) for i in range(3)]
