@@ -363,7 +363,7 @@ int strip_vx(int n, int prec) {
 // the work items).
 static int march_blocks(int n, int prec) {
     const int my = march_rows(prec);
-    const int len = prec == CH_FP64 ? CH_MARCH_L : march_len_fp32(n);
+    const int len = march_len(n, prec);
     const long long items = (long long)((n + 63) / 64) * ((n + my - 1) / my) * ((n + len - 1) / len);
     return (int)std::min<long long>(items, CH_WBLK_MAX);
 }
@@ -393,6 +393,7 @@ Inst make_inst(const Member& m, int i, int dim, int prec, int sblk0, int cblk0, 
     I.wblk0 = wblk0;
     I.wblk = wide_blocks(dim, n, prec);
     I.vx = strip_vx(n, prec);
+    I.zlen = dim == 3 ? march_len(n, prec) : 0;
     I.eps2 = m.eps * m.eps;
     const double inv_h = double(n) / m.sh.length;   // h = L / n
     I.inv_h2 = inv_h * inv_h;

@@ -90,6 +90,7 @@ struct Inst {
     int eyre;
     int wblk0, wblk;    // 2-D row-strip / 3-D marching workgroups [wblk0, wblk0 + wblk)
     int vx;             // 2-D strips: columns per lane (divides n)
+    int zlen;           // 3-D marching kernels: planes per run of a workgroup
     int bc;             // ch_bc
     int mob;            // variable mobility, coefficients in the control block
 };

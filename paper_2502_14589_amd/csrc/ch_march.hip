@@ -10,8 +10,8 @@
 // <u, w>).
 //
 // Layout.  A workgroup owns an MX x MY block of (x, y) columns and a run of
-// up to CH_MARCH_L planes in z (in the FP32 matvec, the length march_len_fp32
-// picks for the grid), which it walks plane by plane.  Thread t owns the same
+// zlen planes in z (march_len of the grid and the basis precision), which it
+// walks plane by plane.  Thread t owns the same
 // 16 bytes of consecutive-x columns of the block in every pass (the stencil
 // passes and the dot phase: two x in FP64, four in FP32), plus one column of
 // the halo-1 ring around the block.  In LDS: a ring of three operand planes
@@ -161,7 +161,7 @@ struct MarchItem {
 };
 
 template <int MX, int MY>
-__device__ __forceinline__ MarchItem march_item(int it, int n, int len = CH_MARCH_L) {
+__device__ __forceinline__ MarchItem march_item(int it, int n, int len) {
     const int ntx = (n + MX - 1) / MX, nty = (n + MY - 1) / MY;
     const int nxy = ntx * nty;
     const int c = it / nxy, t = it - c * nxy;
@@ -197,8 +197,7 @@ template <typename TV, typename TY, bool SINGLE, int TAG, int DV, bool BIGK, boo
 __global__ __launch_bounds__(CH_BLOCK) void k_matvec_m(Ctl* __restrict__ ctls, const Inst* __restrict__ insts,
                                                        const int* __restrict__ wb2i, const Inst inst0, int ninst,
                                                        TV* __restrict__ V, size_t ldv, int k, int store_w,
-                                                       const TY* __restrict__ ybase, double* __restrict__ pout,
-                                                       int zlen0) {
+                                                       const TY* __restrict__ ybase, double* __restrict__ pout) {
     using G = MGeo<TV>;
     constexpr int MX = G::MX, MY = G::MY, MVX = G::MVX, MVP = G::MVP, MQX = G::MQX, MQY = G::MQY, MQS = G::MQS,
                   MQPS = G::MQPS, MVS = G::MVS, MVPS = G::MVPS, PV = G::PV, PQ = G::PQ;
@@ -229,8 +228,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_matvec_m(Ctl* __restrict__ ctls, c
     for (int i = tid; i < nrows * NW; i += CH_BLOCK) red[i / NW][i % NW] = 0.0;
     const int hv = wave_sum8_holder(lane);
     const int ntx = (n + MX - 1) / MX, nty = (n + MY - 1) / MY;
-    // planes per run: from the host for a single grid, else per instance
-    const int zlen = SINGLE ? zlen0 : (sizeof(TV) == 4 ? march_len_fp32(n) : CH_MARCH_L);
+    const int zlen = I.zlen;
     const int nitems = ntx * nty * ((n + zlen - 1) / zlen);
     const int lb = xcd_remap(blockIdx.x - I.wblk0, I.wblk);
     constexpr int RB = 4;   // columns per wave_sum8 (two sums each)
@@ -504,7 +502,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_est_m(Ctl* __restrict__ ctls, cons
                                                     const int* __restrict__ wb2i, const Inst inst0, int ninst,
                                                     const double* __restrict__ y0base, const double* __restrict__ y1base,
                                                     double* __restrict__ fbase, TV* __restrict__ V0base,
-                                                    float* __restrict__ y32base, double* __restrict__ pout, int zlen0) {
+                                                    float* __restrict__ y32base, double* __restrict__ pout) {
     using G = MGeo<double>;
     constexpr int MX = G::MX, MY = G::MY, MVX = G::MVX, MVP = G::MVP, MQX = G::MQX, MQY = G::MQY, MQS = G::MQS,
                   MQPS = G::MQPS;
@@ -529,7 +527,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_est_m(Ctl* __restrict__ ctls, cons
     const int ntx = (n + MX - 1) / MX, nty = (n + MY - 1) / MY;
     // planes per run: the FP32 matvec's in the mixed form (its workgroup
     // count is sized for them); from the host for a single grid
-    const int zlen = SINGLE ? zlen0 : (sizeof(TV) == 4 ? march_len_fp32(n) : CH_MARCH_L);
+    const int zlen = I.zlen;
     const int nitems = ntx * nty * ((n + zlen - 1) / zlen);
     const int lb = xcd_remap(blockIdx.x - I.wblk0, I.wblk);
     int qrx[NQL], qry[NQL];
@@ -763,7 +761,8 @@ __global__ __launch_bounds__(CH_BLOCK) void k_lim_stage_m(Ctl* __restrict__ ctls
     const double ta = cf[0], inv = cf[1];
     const int tid = threadIdx.x;
     const int ntx = (n + MX - 1) / MX, nty = (n + MY - 1) / MY;
-    const int nitems = ntx * nty * ((n + CH_MARCH_L - 1) / CH_MARCH_L);
+    const int zlen = I.zlen;
+    const int nitems = ntx * nty * ((n + zlen - 1) / zlen);
     const int lb = xcd_remap(blockIdx.x - I.wblk0, I.wblk);
     int qrx[NQL], qry[NQL];
     const int cx = NPT * (tid % TXT), cy = tid / TXT;
@@ -792,7 +791,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_lim_stage_m(Ctl* __restrict__ ctls
     auto items = [&](auto vec_c) {
     constexpr bool VEC = decltype(vec_c)::value;
     for (int it = lb; it < nitems; it += I.wblk) {
-        const MarchItem m = march_item<MX, MY>(it, n);
+        const MarchItem m = march_item<MX, MY>(it, n, zlen);
         unsigned vo[NVL], qpos[NQL];
 #pragma unroll
         for (int q = 0; q < NVL; ++q) {
@@ -964,7 +963,8 @@ __global__ __launch_bounds__(CH_BLOCK) void k_est_lim_m(Ctl* __restrict__ ctls, 
     const double half_tau = 0.5 * ctl->tau0;
     const int tid = threadIdx.x;
     const int ntx = (n + MX - 1) / MX, nty = (n + MY - 1) / MY;
-    const int nitems = ntx * nty * ((n + CH_MARCH_L - 1) / CH_MARCH_L);
+    const int zlen = I.zlen;
+    const int nitems = ntx * nty * ((n + zlen - 1) / zlen);
     const int lb = xcd_remap(blockIdx.x - I.wblk0, I.wblk);
     int qrx[NQL], qry[NQL];
     const int cx = NPT * (tid % TXT), cy = tid / TXT;
@@ -995,7 +995,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_est_lim_m(Ctl* __restrict__ ctls, 
     constexpr bool VEC = decltype(vec_c)::value;
     (void)VEC;
     for (int it = lb; it < nitems; it += I.wblk) {
-        const MarchItem m = march_item<MX, MY>(it, n);
+        const MarchItem m = march_item<MX, MY>(it, n, zlen);
         unsigned vo[NVL], qpos[NQL];
 #pragma unroll
         for (int q = 0; q < NVL; ++q) {
@@ -1157,20 +1157,19 @@ template <typename TV, typename TY, bool NT, bool NTW>
 static void launch_matvec_m(const Table& t, const DevBuffers& b, const TY* y, int k, int store_w, double* pout,
                             bool timing, hipStream_t s) {
     TV* V = static_cast<TV*>(b.V);
-    const int zl = sizeof(TV) == 4 ? march_len_fp32(t.hinst[0].n) : CH_MARCH_L;   // single-grid launches
     const bool vec = t.hinst[0].n % MGeo<TV>::NPT == 0;   // the tile pair as one vector
     if (k > CH_MSMALL) {
-        if (timing) hipLaunchKernelGGL((k_matvec_m<TV, TY, true, 1, 2, true, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout, zl);
-        else if (t.ninst == 1) hipLaunchKernelGGL((k_matvec_m<TV, TY, true, 0, 2, true, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout, zl);
-        else hipLaunchKernelGGL((k_matvec_m<TV, TY, false, 0, 2, true, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout, zl);
+        if (timing) hipLaunchKernelGGL((k_matvec_m<TV, TY, true, 1, 2, true, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout);
+        else if (t.ninst == 1) hipLaunchKernelGGL((k_matvec_m<TV, TY, true, 0, 2, true, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout);
+        else hipLaunchKernelGGL((k_matvec_m<TV, TY, false, 0, 2, true, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout);
     } else if (timing) {
-        if (vec) hipLaunchKernelGGL((k_matvec_m<TV, TY, true, 1, 1, false, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout, zl);
-        else hipLaunchKernelGGL((k_matvec_m<TV, TY, true, 1, 0, false, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout, zl);
+        if (vec) hipLaunchKernelGGL((k_matvec_m<TV, TY, true, 1, 1, false, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout);
+        else hipLaunchKernelGGL((k_matvec_m<TV, TY, true, 1, 0, false, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout);
     } else if (t.ninst == 1) {
-        if (vec) hipLaunchKernelGGL((k_matvec_m<TV, TY, true, 0, 1, false, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout, zl);
-        else hipLaunchKernelGGL((k_matvec_m<TV, TY, true, 0, 0, false, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout, zl);
+        if (vec) hipLaunchKernelGGL((k_matvec_m<TV, TY, true, 0, 1, false, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout);
+        else hipLaunchKernelGGL((k_matvec_m<TV, TY, true, 0, 0, false, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout);
     } else {
-        hipLaunchKernelGGL((k_matvec_m<TV, TY, false, 0, 2, false, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout, zl);
+        hipLaunchKernelGGL((k_matvec_m<TV, TY, false, 0, 2, false, NT, NTW>), MARGS, V, b.ldv, k, store_w, y, pout);
     }
 }
 
@@ -1196,14 +1195,13 @@ template <typename TV>
 static void launch_est_m(const Table& t, const DevBuffers& b, const double* y0, const double* y1, float* y32,
                          double* pout, hipStream_t s) {
     TV* V0 = static_cast<TV*>(b.V);
-    const int zl = sizeof(TV) == 4 ? march_len_fp32(t.hinst[0].n) : CH_MARCH_L;   // single-grid launches
     if (t.ninst == 1) {
         if (t.hinst[0].n % MGeo<double>::NPT == 0)
-            hipLaunchKernelGGL((k_est_m<TV, true, 1>), MARGS, y0, y1, b.fcur, V0, y32, pout, zl);
+            hipLaunchKernelGGL((k_est_m<TV, true, 1>), MARGS, y0, y1, b.fcur, V0, y32, pout);
         else
-            hipLaunchKernelGGL((k_est_m<TV, true, 0>), MARGS, y0, y1, b.fcur, V0, y32, pout, zl);
+            hipLaunchKernelGGL((k_est_m<TV, true, 0>), MARGS, y0, y1, b.fcur, V0, y32, pout);
     } else {
-        hipLaunchKernelGGL((k_est_m<TV, false, 2>), MARGS, y0, y1, b.fcur, V0, y32, pout, zl);
+        hipLaunchKernelGGL((k_est_m<TV, false, 2>), MARGS, y0, y1, b.fcur, V0, y32, pout);
     }
 }
 
