@@ -550,7 +550,7 @@ bool all_halted(const ch_ctx* ctx, int n) {
 // The Arnoldi iterations and phi tests of one cycle: resident (ctx->cyc) or
 // as ordinary launches.
 int issue_cycle(ch_ctx* ctx, const Table& t, int prec, PartSeq& ps, const double* y, int m_max, int orth) {
-    if (ctx->cyc.waves > 0) {
+    if (ctx->cyc.strips > 0) {
         int epoch, rc;
         if ((rc = next_epoch(ctx, CYCLE_EPOCHS, &epoch))) return rc;
         HIP_TRY(ctx, launch_cycle(t, prec, ctx->b, ctx->cyc, epoch, y, m_max, ctx->stream));
@@ -566,7 +566,7 @@ void use_resident_cycles(ch_ctx* ctx, const Table& t, int m_max, int orth, int g
     ctx->cyc = CycleShape{0, 0};
     if (orth != CH_ORTH_DCGS2 || graph_chunk > 0) return;
     const CycleShape c = cycle_shape(t, m_max, ctx->cus);
-    if (c.waves > 0 && ensure_resident(ctx, true) == CH_OK && lease->take(ctx->device, ctx->cus, c.workgroups)) ctx->cyc = c;
+    if (c.strips > 0 && ensure_resident(ctx, true) == CH_OK && lease->take(ctx->device, ctx->cus, c.workgroups)) ctx->cyc = c;
 }
 
 // After read_heads: true when a resident cycle gave up waiting.  The run then

@@ -116,10 +116,10 @@ LimTiles lim_tiles(const Inst& I, int cus);
 hipError_t launch_lim_run(const Table& t, const DevBuffers& b, const LimTiles& g, int epoch, const double* yin,
                           double* yout, hipStream_t s);
 
-// Resident Krylov cycle (ch_cycle.hip) of a single 2-D grid: `waves` per
-// workgroup, workgroups in all; waves = 0: the grid or m_max does not fit.
+// Resident Krylov cycle (ch_cycle.hip) of a single 2-D grid: strips per
+// workgroup, workgroups in all; strips = 0: the grid or m_max does not fit.
 struct CycleShape {
-    int waves, workgroups;
+    int strips, workgroups;
 };
 CycleShape cycle_shape(const Table& t, int m_max, int cus);
 size_t cycle_doubles();   // of DevBuffers::cyc

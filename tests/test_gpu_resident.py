@@ -164,3 +164,28 @@ def test_two_threads_share_the_device():
         t.join()
     for g in got:
         assert np.array_equal(g, ref)
+
+
+# two strips to a wave: widths of 1, 2 and 4 columns per lane, and a last workgroup partly or wholly filled
+@pytest.mark.parametrize("n,kind,prec", [(701, "periodic", ch.CH_FP64), (699, "neumann", ch.CH_FP32_MIXED), (1000, "mobility", ch.CH_FP64),
+                                         (1024, "periodic", ch.CH_FP64), (1054, "neumann", ch.CH_FP32_MIXED),
+                                         (1300, "periodic", ch.CH_FP32_MIXED)])
+def test_krylov_cycles_of_two_strips_per_wave(ctx, plain, n, kind, prec):
+    test_krylov_cycles(ctx, plain, n, kind, prec)
+
+
+@pytest.mark.parametrize("prec", [ch.CH_FP64, ch.CH_FP32_MIXED])
+@pytest.mark.parametrize("m_max", [31, 32, 33, 47, 48])
+def test_krylov_dimensions_across_the_test_orders(ctx, plain, m_max, prec):
+    """Dimensions whose tests fill the smaller padded order, the larger one, and exceed it (ordinary launches)."""
+    n = 90
+    p = ch.Problem(2, n, 0.03, precision=prec)
+    y0 = uniform_field(n, 2, 0.1, 0.4, seed=8700 + m_max)
+    rho = p.eps ** 2 * 64.0 * n ** 4
+    out = []
+    for c in (ctx, plain):
+        y = dev(y0)
+        st, recs = c.run_ee(p, y, 0.7 * m_max * m_max / rho, max_steps=2, m_max=m_max, records=True)
+        out.append((y.cpu().numpy(), st, recs))
+    assert out[0][1:] == out[1][1:] and recs[0]["j"] >= min(m_max, 33)   # the larger ones converge before m_max
+    assert np.array_equal(out[0][0], out[1][0])
