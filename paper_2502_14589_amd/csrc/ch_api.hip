@@ -31,6 +31,13 @@
 #include "ch_march.h"
 #include "ch_resident.h"
 
+// Copy of n values (a field to or from the pooled state).
+struct Move {
+    const double* src;
+    double* dst;
+    long long n;
+};
+
 struct ch_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -43,7 +50,7 @@ struct ch_ctx {
     size_t rec_n = 0;        // step records allocated
     int cus = 0;             // compute units of the device
     int epoch = 0;           // last flag value given to a resident launch
-    CycleShape cyc{0, 0};    // resident Krylov cycles of the current call (waves = 0: ordinary launches)
+    CycleShape cyc{0, 0};    // resident Krylov cycles of the current call (strips = 0: ordinary launches)
     int phibig_slots = 0;    // slots of the phi scratch of orders above 48
     ch_step_record* rec = nullptr;
     std::vector<int> expect; // per slot: Krylov cycles issued (compared with the device's `cyc`)
@@ -55,13 +62,13 @@ struct ch_ctx {
     // instance tables: store 0 serves every run; the server keeps the
     // table of its LIM members in store 1 beside that of its EE members
     struct TableStore {
-        Inst* d_inst = nullptr;
-        int* d_sb2i = nullptr;
-        int* d_cb2i = nullptr;
-        int* d_wb2i = nullptr;
-        size_t inst_cap = 0, map_cap = 0;
+        char* dev = nullptr;     // the instances, then the three maps
+        char* host = nullptr;    // pinned image of it
+        size_t cap = 0;          // bytes of each
         std::vector<Inst> h_inst;
     } store[2];
+    Move* moves = nullptr;   // pinned, device-mapped: the field copies of a batch
+    int moves_cap = 0;
     LaunchEnv env{};         // second stream for the DCGS2 phi tests, capture stream, graph switch
     GraphCache graphs;       // captured DCGS2 iterations
     struct ShapeEntry {      // launch shapes set or tuned for (dim, n, prec)
@@ -454,39 +461,29 @@ int build_table(ch_ctx* ctx, const std::vector<Member>& ms, int dim, int prec, T
         ctx->err = "batch too large for one launch (workgroup table)";
         return CH_EINVAL;
     }
-    int rc;
-    if ((size_t)ni > ts.inst_cap) {
-        free_dev(ts.d_inst);
-        ts.d_inst = nullptr;
-        ts.inst_cap = 0;
-        if ((rc = alloc_dev(ctx, (void**)&ts.d_inst, sizeof(Inst) * ni))) return rc;
-        ts.inst_cap = ni;
-    }
-    const size_t mneed = std::max(std::max(sb.size(), cb.size()), std::max(wb.size(), (size_t)1));
-    if (mneed > ts.map_cap) {
-        free_dev(ts.d_sb2i);
-        free_dev(ts.d_cb2i);
-        free_dev(ts.d_wb2i);
-        ts.d_sb2i = ts.d_cb2i = ts.d_wb2i = nullptr;
-        ts.map_cap = 0;
-        if ((rc = alloc_dev(ctx, (void**)&ts.d_sb2i, sizeof(int) * mneed))) return rc;
-        if ((rc = alloc_dev(ctx, (void**)&ts.d_cb2i, sizeof(int) * mneed))) return rc;
-        if ((rc = alloc_dev(ctx, (void**)&ts.d_wb2i, sizeof(int) * mneed))) return rc;
-        ts.map_cap = mneed;
-    }
-    HIP_TRY(ctx, hipMemcpyAsync(ts.d_inst, ts.h_inst.data(), sizeof(Inst) * ni, hipMemcpyHostToDevice,
-                                ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(ts.d_sb2i, sb.data(), sizeof(int) * sb.size(), hipMemcpyHostToDevice, ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(ts.d_cb2i, cb.data(), sizeof(int) * cb.size(), hipMemcpyHostToDevice, ctx->stream));
-    if (!wb.empty())
-        HIP_TRY(ctx, hipMemcpyAsync(ts.d_wb2i, wb.data(), sizeof(int) * wb.size(), hipMemcpyHostToDevice,
-                                    ctx->stream));
-    // the host vectors must outlive the asynchronous copies
+    // one copy from a pinned image, which the previous table's copy may still read
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-    t->inst = ts.d_inst;
-    t->sb2i = ts.d_sb2i;
-    t->cb2i = ts.d_cb2i;
-    t->wb2i = ts.d_wb2i;
+    const size_t at_sb = pad64(sizeof(Inst) * ni), at_cb = at_sb + pad64(sizeof(int) * sb.size()),
+                 at_wb = at_cb + pad64(sizeof(int) * cb.size()), bytes = at_wb + pad64(sizeof(int) * wb.size());
+    if (bytes > ts.cap) {
+        free_dev(ts.dev);
+        if (ts.host) (void)hipHostFree(ts.host);
+        ts.dev = ts.host = nullptr;
+        ts.cap = 0;
+        const int rc = alloc_dev(ctx, (void**)&ts.dev, bytes);
+        if (rc) return rc;
+        HIP_TRY(ctx, hipHostMalloc((void**)&ts.host, bytes, hipHostMallocDefault));
+        ts.cap = bytes;
+    }
+    memcpy(ts.host, ts.h_inst.data(), sizeof(Inst) * ni);
+    memcpy(ts.host + at_sb, sb.data(), sizeof(int) * sb.size());
+    memcpy(ts.host + at_cb, cb.data(), sizeof(int) * cb.size());
+    memcpy(ts.host + at_wb, wb.data(), sizeof(int) * wb.size());
+    HIP_TRY(ctx, hipMemcpyAsync(ts.dev, ts.host, bytes, hipMemcpyHostToDevice, ctx->stream));
+    t->inst = reinterpret_cast<Inst*>(ts.dev);
+    t->sb2i = reinterpret_cast<int*>(ts.dev + at_sb);
+    t->cb2i = reinterpret_cast<int*>(ts.dev + at_cb);
+    t->wb2i = reinterpret_cast<int*>(ts.dev + at_wb);
     t->ninst = ni;
     t->sgrid = (int)sb.size();
     t->cgrid = (int)cb.size();
@@ -496,11 +493,15 @@ int build_table(ch_ctx* ctx, const std::vector<Member>& ms, int dim, int prec, T
     return CH_OK;
 }
 
+// Bytes of the control block's scalar head (everything before the Arnoldi arrays).
+constexpr size_t CTL_HEAD = offsetof(Ctl, H);
+
+// The head of a control block at the start of a run (the rest is zero there).
 // cyc0: the slot's count of Krylov cycles issued so far.  The count only
 // grows (across runs), so a flag left by an earlier run never matches.
-void init_ctl(Ctl* c, int mode, double t0, double tau0, double T, double tol, double tol_phi_fixed, double tau_min,
+void init_head(Ctl* c, int mode, double t0, double tau0, double T, double tol, double tol_phi_fixed, double tau_min,
               int m_max, int max_steps, ch_step_record* rec, int rec_cap, int cyc0) {
-    memset(c, 0, sizeof(Ctl));
+    memset(c, 0, CTL_HEAD);
     c->cyc = cyc0;
     c->mode = mode;
     c->t = t0;
@@ -516,14 +517,18 @@ void init_ctl(Ctl* c, int mode, double t0, double tau0, double T, double tol, do
     c->rec_cap = rec ? rec_cap : 0;
 }
 
+// The whole control block.
+template <typename... Args>
+void init_ctl(Ctl* c, Args... args) {
+    memset(c, 0, sizeof(Ctl));
+    init_head(c, args...);
+}
+
 // The mobility coefficients of a single-grid run (M = 1 unless the problem sets them).
 static void set_mobility(Ctl* c, const Shape& sh) {
     c->mob0 = sh.m0;
     c->mob1 = sh.m1;
 }
-
-// Bytes of the control block's scalar head (everything before the Arnoldi arrays).
-constexpr size_t CTL_HEAD = offsetof(Ctl, H);
 
 // The heads of the control blocks of slots [lo, hi] into hctl: one strided
 // copy (the blocks are contiguous, sizeof(Ctl) apart), then a sync.
@@ -662,6 +667,85 @@ int copy_out(ch_ctx* ctx, const Member& m, int slot, double* y) {
     return CH_OK;
 }
 
+// Zeroes the Arnoldi arrays of the control blocks, one workgroup each.
+__global__ __launch_bounds__(CH_BLOCK) void k_ctl_tail(Ctl* ctls) {
+    double* p = ctls[blockIdx.x].H;
+    constexpr int N = (int)((sizeof(Ctl) - CTL_HEAD) / sizeof(double));
+    for (int i = threadIdx.x; i < N; i += CH_BLOCK) p[i] = 0.0;
+}
+static_assert(CTL_HEAD % sizeof(double) == 0 && sizeof(Ctl) % sizeof(double) == 0, "whole doubles");
+
+// Control blocks of a batch whose heads are in hctl.  Their Arnoldi arrays (83 KB each)
+// are cleared in place: 64 members otherwise clear and upload 5 MB.
+int upload_heads(ch_ctx* ctx, int count) {
+    hipLaunchKernelGGL(k_ctl_tail, dim3(count), dim3(CH_BLOCK), 0, ctx->stream, ctx->b.ctl);
+    HIP_TRY(ctx, hipGetLastError());
+    HIP_TRY(ctx, hipMemcpy2DAsync(ctx->b.ctl, sizeof(Ctl), ctx->hctl, sizeof(Ctl), CTL_HEAD, (size_t)count,
+                                  hipMemcpyHostToDevice, ctx->stream));
+    return CH_OK;
+}
+
+// The field copies of a batch, workgroups (x, member).
+__global__ __launch_bounds__(CH_BLOCK) void k_moves(const Move* __restrict__ moves) {
+    const Move m = moves[blockIdx.y];
+    const long long t = (long long)blockIdx.x * CH_BLOCK + threadIdx.x, nt = (long long)gridDim.x * CH_BLOCK;
+    if (((reinterpret_cast<size_t>(m.src) | reinterpret_cast<size_t>(m.dst)) & 15) == 0) {
+        const double2* s = reinterpret_cast<const double2*>(m.src);
+        double2* d = reinterpret_cast<double2*>(m.dst);
+        for (long long i = t; i < m.n / 2; i += nt) d[i] = s[i];
+        if ((m.n & 1) && t == 0) m.dst[m.n - 1] = m.src[m.n - 1];
+    } else {
+        for (long long i = t; i < m.n; i += nt) m.dst[i] = m.src[i];
+    }
+}
+
+// Copies the members' fields to (in) or from the pooled state.  One launch where every
+// field is memory of this device, apart from the others and aligned to its values; a copy
+// of its own per member (4-5 us of host time each) elsewhere, and for few members.
+int move_fields(ch_ctx* ctx, const std::vector<Member>& ms, const ch_batch_item* items, bool in) {
+    const int count = (int)ms.size();
+    bool one = count >= 4 && count <= 65535;
+    std::vector<std::pair<size_t, size_t>> at(one ? count : 0);
+    for (int i = 0; one && i < count; ++i) {
+        hipPointerAttribute_t a;
+        at[i] = {reinterpret_cast<size_t>(items[i].y), sizeof(double) * ms[i].sh.N};
+        one = at[i].first % sizeof(double) == 0 && hipPointerGetAttributes(&a, items[i].y) == hipSuccess &&
+              a.type == hipMemoryTypeDevice && a.device == ctx->device;
+    }
+    (void)hipGetLastError();   // a pointer the runtime does not know
+    if (one) {
+        std::sort(at.begin(), at.end());
+        for (int i = 0; one && i + 1 < count; ++i) one = at[i].first + at[i].second <= at[i + 1].first;
+    }
+    if (one && count > ctx->moves_cap) {
+        if (ctx->moves) (void)hipHostFree(ctx->moves);
+        ctx->moves = nullptr;
+        ctx->moves_cap = 0;
+        if (hipHostMalloc((void**)&ctx->moves, sizeof(Move) * count, hipHostMallocMapped) == hipSuccess) ctx->moves_cap = count;
+        else one = false;
+    }
+    if (!one) {
+        for (int i = 0; i < count; ++i) {
+            const int rc = in ? copy_in(ctx, ms[i], items[i].y) : copy_out(ctx, ms[i], i, items[i].y);
+            if (rc) return rc;
+        }
+        return CH_OK;
+    }
+    long long most = 0;
+    for (int i = 0; i < count; ++i) {
+        const long long N = ms[i].sh.N;
+        double* pool = ctx->b.ybuf[in ? 0 : ctx->hctl[i].cur] + ms[i].off;
+        ctx->moves[i] = in ? Move{items[i].y, pool, N} : Move{pool, items[i].y, N};
+        most = std::max(most, N);
+    }
+    Move* dev = nullptr;
+    HIP_TRY(ctx, hipHostGetDevicePointer((void**)&dev, ctx->moves, 0));
+    const unsigned x = (unsigned)std::min<long long>((most + 8 * CH_BLOCK - 1) / (8 * CH_BLOCK), 256);
+    hipLaunchKernelGGL(k_moves, dim3(x, count), dim3(CH_BLOCK), 0, ctx->stream, dev);
+    HIP_TRY(ctx, hipGetLastError());
+    return CH_OK;
+}
+
 int run_ee(ch_ctx* ctx, const ch_problem* prob, double* y, double tau0, double t0, double T, int max_steps,
            const ch_ee_opts* opts, ch_run_stats* stats, ch_step_record* records) {
     Shape sh;
@@ -737,12 +821,11 @@ int run_ee_batch(ch_ctx* ctx, int count, const ch_batch_item* items, int dim, in
     long long limit = 0;
     for (int i = 0; i < count; ++i) {
         const ch_batch_item& it = items[i];
-        init_ctl(ctx->hctl + i, MODE_EE, 0.0, it.tau0, it.T, opts->tol, opts->tol_phi_fixed, opts->tau_min,
-                 opts->m_max, it.max_steps, nullptr, 0, ctx->expect[i]);
+        init_head(ctx->hctl + i, MODE_EE, 0.0, it.tau0, it.T, opts->tol, opts->tol_phi_fixed, opts->tau_min,
+                  opts->m_max, it.max_steps, nullptr, 0, ctx->expect[i]);
         limit = it.max_steps > 0 ? std::max<long long>(limit, it.max_steps) : (1LL << 40);
-        if ((rc = copy_in(ctx, ms[i], it.y))) return rc;
     }
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->b.ctl, ctx->hctl, sizeof(Ctl) * count, hipMemcpyHostToDevice, ctx->stream));
+    if ((rc = move_fields(ctx, ms, items, true)) || (rc = upload_heads(ctx, count))) return rc;
     ctx->cyc = CycleShape{0, 0};
     ctx->env.graph_chunk = opts->graph_chunk;
     rc = issue_ee_steps(ctx, t, prec, opts->m_max, opts->orth, false, limit);
@@ -750,8 +833,8 @@ int run_ee_batch(ch_ctx* ctx, int count, const ch_batch_item* items, int dim, in
     if (rc) return rc;
     if ((rc = read_heads(ctx, count))) return rc;
     int status = CH_OK;
+    if ((rc = move_fields(ctx, ms, items, false))) return rc;
     for (int i = 0; i < count; ++i) {
-        if ((rc = copy_out(ctx, ms[i], i, items[i].y))) return rc;
         if (stats) fill_stats(ctx->hctl[i], stats + i);
         if (ctx->hctl[i].status != CH_OK && status == CH_OK) status = ctx->hctl[i].status;
     }
@@ -940,11 +1023,10 @@ int run_lim_batch(ch_ctx* ctx, int count, const ch_batch_item* items, int dim, i
     const DevBuffers& b = ctx->b;
     for (int i = 0; i < count; ++i) {
         const ch_batch_item& it = items[i];
-        init_ctl(ctx->hctl + i, tol > 0.0 ? MODE_LIM : MODE_LIM_CONST, 0.0, it.tau0, it.T, tol, 0.0, 0.0, 0,
-                 it.max_steps, nullptr, 0, ctx->expect[i]);
-        if ((rc = copy_in(ctx, ms[i], it.y))) return rc;
+        init_head(ctx->hctl + i, tol > 0.0 ? MODE_LIM : MODE_LIM_CONST, 0.0, it.tau0, it.T, tol, 0.0, 0.0, 0,
+                  it.max_steps, nullptr, 0, ctx->expect[i]);
     }
-    HIP_TRY(ctx, hipMemcpyAsync(b.ctl, ctx->hctl, sizeof(Ctl) * count, hipMemcpyHostToDevice, ctx->stream));
+    if ((rc = move_fields(ctx, ms, items, true)) || (rc = upload_heads(ctx, count))) return rc;
     PartSeq ps;
     ps.base = b.part;
     for (long long s = 0;; ++s) {
@@ -954,8 +1036,8 @@ int run_lim_batch(ch_ctx* ctx, int count, const ch_batch_item* items, int dim, i
     }
     if ((rc = read_heads(ctx, count))) return rc;
     int status = CH_OK;
+    if ((rc = move_fields(ctx, ms, items, false))) return rc;
     for (int i = 0; i < count; ++i) {
-        if ((rc = copy_out(ctx, ms[i], i, items[i].y))) return rc;
         if (stats) fill_stats(ctx->hctl[i], stats + i);
         if (ctx->hctl[i].status != CH_OK && status == CH_OK) status = ctx->hctl[i].status;
     }
@@ -1395,8 +1477,11 @@ int ch_destroy(ch_ctx* ctx) {
                     (void*)b.part, (void*)b.dots, (void*)b.lorder, (void*)b.ctl, (void*)ctx->rec, b.phibig,
                     (void*)b.lcoef, (void*)b.dcount, (void*)b.flags, (void*)b.cyc})
         free_dev(p);
-    for (auto& ts : ctx->store)
-        for (void* p : {(void*)ts.d_inst, (void*)ts.d_sb2i, (void*)ts.d_cb2i, (void*)ts.d_wb2i}) free_dev(p);
+    for (auto& ts : ctx->store) {
+        free_dev(ts.dev);
+        if (ts.host) (void)hipHostFree(ts.host);
+    }
+    if (ctx->moves) (void)hipHostFree(ctx->moves);
     if (ctx->hctl) (void)hipHostFree(ctx->hctl);
     if (ctx->hflag) (void)hipHostFree(ctx->hflag);
     (void)hipEventDestroy(ctx->env.ev_main);
