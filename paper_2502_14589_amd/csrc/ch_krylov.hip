@@ -879,13 +879,65 @@ __device__ __forceinline__ double wave_reduce_rl(double x, Op op) {
     return op(op(readlane_d(x, 0), readlane_d(x, 16)), op(readlane_d(x, 32), readlane_d(x, 48)));
 }
 
+// Up to 64 K nodes in the lanes of one wave, node lane + 64 k in sc[k]: no
+// barrier, and of the two reductions of a pick the second (the smallest index) is a
+// scalar scan of ballots.  Same sums, maxima and picks.  A pick is a chain of LDS
+// reads, sums and one reduction of about 0.31 us at K = 4, against 0.86 by the workgroup
+// with its two barriers: the plan at p = 191 173 -> 70 us.
+constexpr int LEJA_WAVE_K = 16;
+static_assert(3 * 64 * LEJA_WAVE_K + 128 <= 2 * CH_PMAX, "table of log-distances");
+
+template <int K>
+__device__ __forceinline__ void leja_wave(int p, int* __restrict__ order, const double* L) {
+    const double log2 = 0.6931471805599453;
+    const int lane = threadIdx.x & 63;
+    double sc[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) sc[k] = lane + 64 * k < p ? 0.0 : -__builtin_inf();
+    int r = 0;
+    for (int s = 0; s < p; ++s) {
+        if (lane == 0) order[s] = r;
+        double t[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int i = lane + 64 * k, d = i - r;
+            t[k] = log2 + (L[i + r + 1] + L[d < 0 ? -d : d]);
+        }
+        double best = -__builtin_inf();
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            sc[k] = (sc[k] + t[k]) + (lane + 64 * k == r ? -__builtin_inf() : 0.0);
+            best = fmax(best, sc[k]);
+        }
+        if (s == p - 1) break;
+        best = wave_reduce_rl(best, [](double x, double y) { return fmax(x, y); });
+        const double lim = best - 1e-9 * fmax(1.0, fabs(best));
+#pragma unroll
+        for (int k = K - 1; k >= 0; --k) {
+            const unsigned long long m = __ballot(sc[k] >= lim);
+            if (m) r = 64 * k + __builtin_ctzll(m);
+        }
+    }
+}
+
 __device__ __forceinline__ void lim_leja_order(int p, int* __restrict__ order) {
     constexpr int K = CH_PMAX / CH_BLOCK, G = 8, NW = CH_BLOCK / 64;
     __shared__ double L[2 * CH_PMAX];
     __shared__ double wmax[NW], wmin[NW];
     const double pi = 3.141592653589793, log2 = 0.6931471805599453;
-    for (int k = threadIdx.x; k < 2 * CH_PMAX; k += CH_BLOCK)
+    // one wave's nodes, padded to 64 K < 2p + 128, reach entry 3p + 128
+    const int nl = p <= 64 * LEJA_WAVE_K ? 3 * p + 128 : 2 * CH_PMAX;
+    for (int k = threadIdx.x; k < nl; k += CH_BLOCK)
         L[k] = (k == 0 || k >= 2 * p) ? 0.0 : log(sin(pi * double(k) / double(2 * p)));
+    __syncthreads();
+    if (p <= 64 * LEJA_WAVE_K) {
+        if (threadIdx.x >= 64) return;
+        if (p <= 64 * 2) leja_wave<2>(p, order, L);
+        else if (p <= 64 * 4) leja_wave<4>(p, order, L);
+        else if (p <= 64 * 8) leja_wave<8>(p, order, L);
+        else leja_wave<LEJA_WAVE_K>(p, order, L);
+        return;
+    }
     // Thread t owns nodes t + CH_BLOCK k, in groups of G whose table reads are
     // in flight together.  Taken nodes and nodes past p hold -inf, which no
     // update or comparison changes.
@@ -894,7 +946,6 @@ __device__ __forceinline__ void lim_leja_order(int p, int* __restrict__ order) {
     double sc[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) sc[k] = tid + CH_BLOCK * k < p ? 0.0 : -__builtin_inf();
-    __syncthreads();
     int r = 0;
     for (int s = 0; s < p; ++s) {
         if (tid == 0) order[s] = r;
