@@ -133,7 +133,9 @@ typedef struct {
     /* DCGS2 only: > 0 issues the Arnoldi iterations of a cycle as HIP graphs of
      * graph_chunk iterations each (1..CH_MMAX + 1), captured once per context,
      * instance table and buffers and then replayed; 0 launches every kernel
-     * directly.  The launches and their results are the same either way. */
+     * directly, or, for a single 2-D grid that fits the device (up to about 1050^2
+     * in FP64, 1500^2 in FP32) with m_max <= 47, a cycle's iterations and tests as one
+     * launch.  The results are the same each way. */
     int graph_chunk;
 } ch_ee_opts;
 

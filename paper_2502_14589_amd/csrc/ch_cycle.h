@@ -704,9 +704,13 @@ hipError_t launch_cycle_t(const Table& t, const CycleArgs& a0, hipStream_t s) {
     const size_t head = (sizeof(CycCoef) + 15) / 16 * 16, red = sizeof(double) * CYC_ROWS * NW * S;
     const size_t col = sizeof(TV) * NW * S * SR * 64 * VX;
     constexpr int RC = cyc_reg_cols(NW, S);
-    const int lds_cols = std::min((int)((CYC_LDS - head - red) / col - 1) / (S > 1 ? 1 : 4) * (S > 1 ? 1 : 4), std::max(0, (A.m_max - RC + 3) / 4 * 4));
+    // u and the columns that fit beside it; with one strip to a wave whole blocks of four (a
+    // mixed block costs registers: 41 spilled at twelve waves, 920 us a cycle instead of 700)
+    constexpr int Q = S > 1 ? 1 : 4;
+    const int lds_cols = std::min((int)((CYC_LDS - head - red) / col - 1) / Q * Q, std::max(0, (A.m_max - RC + 3) / 4 * 4));
     A.lc = RC + lds_cols;
-    const size_t bytes = head + std::max(red + (1 + lds_cols) * col, A.m_max < CYC_NPS ? sizeof(PhiShared<CYC_NPS>) : sizeof(PhiShared<NPMAX>));
+    const size_t phi = A.m_max < CYC_NPS ? sizeof(PhiShared<CYC_NPS>) : sizeof(PhiShared<NPMAX>);
+    const size_t bytes = head + std::max(red + (1 + lds_cols) * col, phi);
     const auto f = k_cycle<TV, NW, S, VX, NEU, MOB>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)CYC_LDS);
