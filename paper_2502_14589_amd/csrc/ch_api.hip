@@ -48,6 +48,7 @@ struct ch_ctx {
     size_t z_pts = 0;
     int slots = 0;           // control blocks allocated
     size_t rec_n = 0;        // step records allocated
+    int part_ld = 0, dots_ld = 0;   // row lengths b.part and b.dots have room for
     int cus = 0;             // compute units of the device
     int epoch = 0;           // last flag value given to a resident launch
     CycleShape cyc{0, 0};    // resident Krylov cycles of the current call (strips = 0: ordinary launches)
@@ -162,9 +163,11 @@ int ensure(ch_ctx* ctx, size_t pts, int m_max, int prec, int nslots, size_t recs
     int rc;
     if (!b.part) {
         if ((rc = alloc_dev(ctx, (void**)&b.part, 2 * sizeof(double) * CH_NRED * CH_MAXB))) return rc;
+        ctx->part_ld = CH_MAXB;
     }
     if (!b.dots) {
         if ((rc = alloc_dev(ctx, (void**)&b.dots, sizeof(double) * CH_DROWS * CH_MAXB))) return rc;
+        ctx->dots_ld = CH_MAXB;
     }
     if (nslots > ctx->slots) {
         free_dev(b.ctl);
@@ -263,6 +266,34 @@ int ensure(ch_ctx* ctx, size_t pts, int m_max, int prec, int nslots, size_t recs
         ctx->rec_n = recs;
     }
     return CH_OK;
+}
+
+// Room for partials in rows of `pld` (tables of very many runs; most have CH_MAXB).
+int grow_partials(ch_ctx* ctx, int pld, bool dots) {
+    DevBuffers& b = ctx->b;
+    int rc;
+    if (pld > ctx->part_ld) {
+        free_dev(b.part);
+        b.part = nullptr;
+        ctx->part_ld = 0;
+        if ((rc = alloc_dev(ctx, (void**)&b.part, 2 * sizeof(double) * CH_NRED * (size_t)pld))) return rc;
+        ctx->part_ld = pld;
+    }
+    if (dots && pld > ctx->dots_ld) {
+        free_dev(b.dots);
+        b.dots = nullptr;
+        ctx->dots_ld = 0;
+        if ((rc = alloc_dev(ctx, (void**)&b.dots, sizeof(double) * CH_DROWS * (size_t)pld))) return rc;
+        ctx->dots_ld = pld;
+    }
+    return CH_OK;
+}
+
+PartSeq partials_of(const DevBuffers& b, const Table& t) {
+    PartSeq ps;
+    ps.base = b.part;
+    ps.ld = (size_t)t.pld;
+    return ps;
 }
 
 // CUs of each device held by resident launches (ch_resident.h) of this
@@ -397,10 +428,12 @@ Inst make_inst(const Member& m, int i, int dim, int prec, int sblk0, int cblk0, 
     I.sblk = sblk;
     I.cblk0 = cblk0;
     I.cblk = cblk;
-    I.wblk0 = wblk0;
-    I.wblk = wide_blocks(dim, n, prec);
+    I.wblk0 = I.zblk0 = wblk0;
+    I.wblk = I.zblk = wide_blocks(dim, n, prec);
     I.vx = strip_vx(n, prec);
     I.zlen = dim == 3 ? march_len(n, prec) : 0;
+    I.zgrp = 1;
+    I.pld = CH_MAXB;
     I.eps2 = m.eps * m.eps;
     const double inv_h = double(n) / m.sh.length;   // h = L / n
     I.inv_h2 = inv_h * inv_h;
@@ -439,28 +472,51 @@ const ch_shape* find_shape(const ch_ctx* ctx, int dim, int n, int prec) {
 }
 
 // Workgroup ranges of each instance and the block-to-instance maps, kept in
-// table store `which` of the context.
-int build_table(ch_ctx* ctx, const std::vector<Member>& ms, int dim, int prec, Table* t, int which = 0) {
+// table store `which` of the context.  lim: the table of a LIM run.
+int build_table(ch_ctx* ctx, const std::vector<Member>& ms, int dim, int prec, Table* t, bool lim = false, int which = 0) {
     const int ni = (int)ms.size();
     ch_ctx::TableStore& ts = ctx->store[which];
     ts.h_inst.assign(ni, Inst{});
-    std::vector<int> sb, cb, wb;
+    // A 3-D FP64 grid in its built-in shape has a partial per run, however short its runs; the
+    // rows of partials are as long as the batch needs, and only the others count for
+    // the limit (its stencil tiles, at least as many as its runs of CH_MARCH_L planes, do).
+    const bool march64 = dim == 3 && prec == CH_FP64;
+    std::vector<char> built_in(ni, 0);
+    long long sn = 0, cn = 0, wn = 0, part = 0, planes = 0;
     for (int i = 0; i < ni; ++i) {
         Inst& I = ts.h_inst[i];
-        I = make_inst(ms[i], i, dim, prec, (int)sb.size(), (int)cb.size(), (int)wb.size());
+        I = make_inst(ms[i], i, dim, prec, (int)sn, (int)cn, (int)part);
         if (const ch_shape* sp = find_shape(ctx, dim, ms[i].sh.n, prec)) {
             I.vx = sp->vx;
             I.wblk = sp->wblk;
             I.cblk = sp->cblk;
+        } else {
+            built_in[i] = march64;
         }
-        sb.insert(sb.end(), I.sblk, i);
-        cb.insert(cb.end(), I.cblk, i);
-        wb.insert(wb.end(), I.wblk, i);
+        if (march64) planes += march_planes(I.n);
+        sn += I.sblk;
+        cn += I.cblk;
+        part += I.wblk;
+        if (!built_in[i]) wn += I.wblk;
     }
-    if (sb.size() > (size_t)CH_MAXB || cb.size() > (size_t)CH_MAXB || wb.size() > (size_t)CH_MAXB) {
+    if (sn > CH_MAXB || cn > CH_MAXB || wn > CH_MAXB) {
         ctx->err = "batch too large for one launch (workgroup table)";
         return CH_EINVAL;
     }
+    const int pld = part > CH_MAXB ? (int)pad64((size_t)part) : CH_MAXB;
+    std::vector<int> sb, cb, wb;
+    for (int i = 0; i < ni; ++i) {
+        Inst& I = ts.h_inst[i];
+        I.pld = pld;
+        I.zgrp = built_in[i] && ni > 1 ? march_group(I.n, I.zlen, planes, lim) : 1;
+        I.zblk0 = (int)wb.size();
+        I.zblk = I.zgrp > 1 ? march_groups(I.n, I.zlen, I.zgrp) : I.wblk;
+        sb.insert(sb.end(), I.sblk, i);
+        cb.insert(cb.end(), I.cblk, i);
+        wb.insert(wb.end(), I.zblk, i);
+    }
+    const int rg = grow_partials(ctx, pld, !lim);
+    if (rg) return rg;
     // one copy from a pinned image, which the previous table's copy may still read
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     const size_t at_sb = pad64(sizeof(Inst) * ni), at_cb = at_sb + pad64(sizeof(int) * sb.size()),
@@ -488,6 +544,7 @@ int build_table(ch_ctx* ctx, const std::vector<Member>& ms, int dim, int prec, T
     t->sgrid = (int)sb.size();
     t->cgrid = (int)cb.size();
     t->wgrid = (int)wb.size();
+    t->pld = pld;
     t->dim = dim;
     t->hinst = ts.h_inst.data();
     return CH_OK;
@@ -631,8 +688,7 @@ bool graph_chunk_ok(const ch_ee_opts* o) { return o->graph_chunk >= 0 && o->grap
 int issue_ee_steps(ch_ctx* ctx, const Table& t, int prec, int m_max, int orth, bool constant, long long max_launch,
                    long long done = 0) {
     const DevBuffers& b = ctx->b;
-    PartSeq ps;
-    ps.base = b.part;
+    PartSeq ps = partials_of(b, t);
     int rc;
     const double* y0 = b.ybuf[done & 1];
     HIP_TRY(ctx, launch_resid(t, prec, b, ps, y0, y0, true, true, ctx->stream));
@@ -965,15 +1021,14 @@ int run_lim(ch_ctx* ctx, const ch_problem* prob, double* y, double tau0, double 
     if ((rc = ensure(ctx, pad64(sh.N), 0, CH_FP64, 1, recs, true))) return rc;
     Member m{sh, prob->eps, prob->eyre, 0};
     Table t;
-    if ((rc = build_table(ctx, {m}, sh.dim, CH_FP64, &t))) return rc;
+    if ((rc = build_table(ctx, {m}, sh.dim, CH_FP64, &t, true))) return rc;
     const DevBuffers& b = ctx->b;
     init_ctl(ctx->hctl, tol > 0.0 ? MODE_LIM : MODE_LIM_CONST, t0, tau0, T, tol, 0.0, 0.0, 0, max_steps,
              recs ? ctx->rec : nullptr, recs, ctx->expect[0]);
     set_mobility(ctx->hctl, sh);
     HIP_TRY(ctx, hipMemcpyAsync(b.ctl, ctx->hctl, sizeof(Ctl), hipMemcpyHostToDevice, ctx->stream));
     if ((rc = copy_in(ctx, m, y))) return rc;
-    PartSeq ps;
-    ps.base = b.part;
+    PartSeq ps = partials_of(b, t);
     long long s0 = 0;
     bool done = false;
     ResidentLease lease;   // held until the call returns: its stream has drained then
@@ -1019,7 +1074,7 @@ int run_lim_batch(ch_ctx* ctx, int count, const ch_batch_item* items, int dim, i
     int rc;
     if ((rc = ensure(ctx, pts, 0, CH_FP64, count, 0, true))) return rc;
     Table t;
-    if ((rc = build_table(ctx, ms, dim, CH_FP64, &t))) return rc;
+    if ((rc = build_table(ctx, ms, dim, CH_FP64, &t, true))) return rc;
     const DevBuffers& b = ctx->b;
     for (int i = 0; i < count; ++i) {
         const ch_batch_item& it = items[i];
@@ -1027,8 +1082,7 @@ int run_lim_batch(ch_ctx* ctx, int count, const ch_batch_item* items, int dim, i
                   it.max_steps, nullptr, 0, ctx->expect[i]);
     }
     if ((rc = move_fields(ctx, ms, items, true)) || (rc = upload_heads(ctx, count))) return rc;
-    PartSeq ps;
-    ps.base = b.part;
+    PartSeq ps = partials_of(b, t);
     for (long long s = 0;; ++s) {
         bool halted = false;
         if ((rc = issue_lim_step(ctx, t, b, ps, ctx->hctl, s, &halted))) return rc;
@@ -1258,8 +1312,7 @@ int serve_once(ch_server* S, long long* par, Table* t, bool* dirty) {
         if (!ms.empty()) {
             Table ta;
             if ((rc = build_table(ctx, ms, 2, S->prec, &ta))) return rc;
-            PartSeq ps;
-            ps.base = b.part;
+            PartSeq ps = partials_of(b, ta);
             HIP_TRY(ctx, launch_resid(ta, S->prec, b, ps, b.ybuf[p], b.ybuf[p], true, true, ctx->stream));
             HIP_TRY(ctx, launch_after_resid(ta, b, ps, true, ctx->stream));
             for (Req* r : admitted)
@@ -1275,13 +1328,12 @@ int serve_once(ch_server* S, long long* par, Table* t, bool* dirty) {
         std::vector<Member> me, ml;
         for (Req* r : ee) me.push_back(member_of(r));
         for (Req* r : lim) ml.push_back(member_of(r));
-        if (!me.empty() && (rc = build_table(ctx, me, 2, S->prec, &t[0], 0))) return rc;
-        if (!ml.empty() && (rc = build_table(ctx, ml, 2, CH_FP64, &t[1], 1))) return rc;
+        if (!me.empty() && (rc = build_table(ctx, me, 2, S->prec, &t[0], false, 0))) return rc;
+        if (!ml.empty() && (rc = build_table(ctx, ml, 2, CH_FP64, &t[1], true, 1))) return rc;
         *dirty = false;
     }
     if (!ee.empty()) {
-        PartSeq ps;
-        ps.base = b.part;
+        PartSeq ps = partials_of(b, t[0]);
         HIP_TRY(ctx, launch_arnoldi(t[0], S->prec, b, ps, b.ybuf[p], S->opts.m_max, S->opts.orth, ctx->expect.data(),
                                     &ctx->env, ctx->stream));
         HIP_TRY(ctx, launch_update(t[0], S->prec, b, b.ybuf[p], b.ybuf[p ^ 1], S->opts.orth == CH_ORTH_DCGS2,
@@ -1291,8 +1343,7 @@ int serve_once(ch_server* S, long long* par, Table* t, bool* dirty) {
         for (Req* r : ee) ctx->expect[r->slot] += 1;
     }
     if (!lim.empty()) {
-        PartSeq ps;
-        ps.base = b.part;
+        PartSeq ps = partials_of(b, t[1]);
         bool halted = false;
         if ((rc = issue_lim_step(ctx, t[1], b, ps, ctx->hctl, *par, &halted))) return rc;
     }
@@ -1592,7 +1643,8 @@ int ch_step_lim_noalloc(ch_ctx* ctx, const ch_problem* prob, double* y, double t
     tb.ninst = 1;
     tb.sgrid = I.sblk;
     tb.cgrid = I.cblk;
-    tb.wgrid = I.wblk;
+    tb.wgrid = I.zblk;
+    tb.pld = I.pld;
     tb.dim = sh.dim;
     tb.hinst = &I;
     Ctl* h = &na_hctl;
@@ -1604,8 +1656,7 @@ int ch_step_lim_noalloc(ch_ctx* ctx, const ch_problem* prob, double* y, double t
     HIP_TRY(ctx, hipMemcpyAsync(dmap, na_zero_map, sizeof(na_zero_map), hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(ctx, hipMemcpyAsync(b.ctl, h, sizeof(Ctl), hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(ctx, hipMemcpyAsync(b.ybuf[0], y, sizeof(double) * sh.N, hipMemcpyDeviceToDevice, ctx->stream));
-    PartSeq ps;
-    ps.base = b.part;
+    PartSeq ps = partials_of(b, tb);
     bool halted = false;
     if ((rc = issue_lim_step(ctx, tb, b, ps, h, 0, &halted))) return rc;
     if ((rc = read_head(ctx, b, h))) return rc;
@@ -1640,8 +1691,7 @@ int ch_phiv(ch_ctx* ctx, const ch_problem* prob, const double* y, double* y_out,
     set_mobility(ctx->hctl, sh);
     HIP_TRY(ctx, hipMemcpyAsync(b.ctl, ctx->hctl, sizeof(Ctl), hipMemcpyHostToDevice, ctx->stream));
     if ((rc = copy_in(ctx, m, y))) return rc;
-    PartSeq ps;
-    ps.base = b.part;
+    PartSeq ps = partials_of(b, t);
     ResidentLease lease;
     use_resident_cycles(ctx, t, m_max, CH_ORTH_DCGS2, 0, &lease);
     for (bool again = true; again;) {
@@ -1741,8 +1791,7 @@ static int time_kernel_core(ch_ctx* ctx, const Shape& sh, const ch_problem* prob
     const double N = double(sh.N);
     double bytes = 0.0;
     auto launch = [&](int k) -> hipError_t {
-        PartSeq ps;
-        ps.base = b.part;
+        PartSeq ps = partials_of(b, t);
         switch (kernel) {
             case CH_KERNEL_MGS:
                 bytes += 4.0 * esz * N;   // read w, v_{i-1}, v_i; write w
@@ -1980,8 +2029,7 @@ int ch_tune_batch_shapes(ch_ctx* ctx, int count, const ch_batch_item* items, int
         Table t;
         int r = build_table(ctx, ms, dim, prec, &t);
         if (r) return r;
-        PartSeq ps;
-        ps.base = b.part;
+        PartSeq ps = partials_of(b, t);
         const int its[3] = {1, m_max / 2, m_max - 1};
         hipEvent_t e0 = nullptr, e1 = nullptr;
         float ms_ = 0.f;

@@ -153,14 +153,15 @@ __device__ __forceinline__ void block_reduce(double (&x)[NR], double (*lds)[NR])
 // orders and publishes the writes -- sums the partials in a fixed order in
 // every workgroup.  Deterministic: each consumer workgroup sees the same total.
 // Slots alternate between consecutive producers (ping-pong), so a consumer
-// never overwrites the partials it is still reading.
+// never overwrites the partials it is still reading.  ld: distance of the sums'
+// rows (Inst::pld); at: the partial's position in them.
 template <int NR, int OP>
-__device__ __forceinline__ void write_partials(double (&x)[NR], double* __restrict__ pout) {
+__device__ __forceinline__ void write_partials(double (&x)[NR], double* __restrict__ pout, int ld, int at) {
     __shared__ double lds[16][NR];
     block_reduce<NR, OP>(x, lds);
     if (threadIdx.x == 0) {
 #pragma unroll
-        for (int r = 0; r < NR; ++r) pout[r * CH_MAXB + blockIdx.x] = x[r];
+        for (int r = 0; r < NR; ++r) pout[(size_t)r * ld + at] = x[r];
     }
 }
 
@@ -169,7 +170,7 @@ __device__ __forceinline__ void write_partials(double (&x)[NR], double* __restri
 // at once (one memory latency), then adds them in a fixed order.
 #define CH_PART_PER_THREAD 8
 template <int NR, int OP>
-__device__ __forceinline__ void sum_partials(const double* __restrict__ pin, int p0, int np, double (&tot)[NR]) {
+__device__ __forceinline__ void sum_partials(const double* __restrict__ pin, int ld, int p0, int np, double (&tot)[NR]) {
     __shared__ double lds[16][NR];
     __shared__ double res[NR];
     double v[NR][CH_PART_PER_THREAD];
@@ -177,7 +178,7 @@ __device__ __forceinline__ void sum_partials(const double* __restrict__ pin, int
     for (int u = 0; u < CH_PART_PER_THREAD; ++u) {
         const int b = threadIdx.x + u * CH_BLOCK;
 #pragma unroll
-        for (int r = 0; r < NR; ++r) v[r][u] = b < np ? pin[r * CH_MAXB + p0 + b] : red_identity<OP>();
+        for (int r = 0; r < NR; ++r) v[r][u] = b < np ? pin[(size_t)r * ld + p0 + b] : red_identity<OP>();
     }
     double s[NR];
 #pragma unroll
@@ -202,11 +203,11 @@ template <int NR, int OP>
 __device__ __forceinline__ void sum_inst_partials(const double* __restrict__ pin, const Inst& I, int kind,
                                                   double (&tot)[NR]) {
     if (kind == PK_TILE)
-        sum_partials<NR, OP>(pin, I.sblk0, I.sblk, tot);
+        sum_partials<NR, OP>(pin, I.pld, I.sblk0, I.sblk, tot);
     else if (kind == PK_STRIP)
-        sum_partials<NR, OP>(pin, I.wblk0, I.wblk, tot);
+        sum_partials<NR, OP>(pin, I.pld, I.wblk0, I.wblk, tot);
     else
-        sum_partials<NR, OP>(pin, I.cblk0, I.cblk, tot);
+        sum_partials<NR, OP>(pin, I.pld, I.cblk0, I.cblk, tot);
 }
 
 // ---------------------------------------------------------------------------
@@ -260,6 +261,13 @@ __device__ __forceinline__ int xcd_remap(int bid, int G) {
     const int q = G >> 3, r = G & 7;
     const int x = bid & 7, local = bid >> 3;
     return x * q + min(x, r) + local;
+}
+
+// Launch position of the workgroup that xcd_remap sends to lb, of G.
+__device__ __forceinline__ int xcd_unmap(int lb, int G) {
+    const int q = G >> 3, r = G & 7, big = r * (q + 1);
+    const int x = lb < big ? lb / (q + 1) : r + (lb - big) / (q > 0 ? q : 1);
+    return (lb - (x * q + min(x, r))) * 8 + x;
 }
 
 template <int DIM>

@@ -175,13 +175,6 @@ __device__ __forceinline__ double* cyc_part(const CycleArgs& A, int k, int row, 
     return A.part + (size_t)(k & 1) * CYC_PART + ((row / CYC_LINE) * CYC_GROUPS + g) * CYC_LINE + row % CYC_LINE;
 }
 
-// Launch position of the workgroup that xcd_remap sends to lb, of G.
-__device__ __forceinline__ int xcd_unmap(int lb, int G) {
-    const int q = G >> 3, r = G & 7, big = r * (q + 1);
-    const int x = lb < big ? lb / (q + 1) : r + (lb - big) / (q > 0 ? q : 1);
-    return (lb - (x * q + min(x, r))) * 8 + x;
-}
-
 // One wave: wave w's share of the sum over row `row` of iteration k, as
 // sum_partials (k_dots_reduce) adds it.
 __device__ __forceinline__ int cyc_reduce(const CycleArgs& A, int k, int row, int w) {

@@ -7,22 +7,17 @@
 
 
 #include "../../include/ch.h"
+#include "ch_runs.h"
 
 #define CH_LDH (CH_MMAX + 1)     // leading dimension of the Hessenberg matrix
-#define CH_MAXB 32768            // most workgroups of a reducing launch (partials per reduction)
+#define CH_MAXB 32768            // most workgroups of a launch over a table (3-D FP64 tables: Inst::pld)
 #define CH_SBLK_MAX 2048         // most stencil workgroups per instance (larger grids loop over tiles);
-#ifndef CH_WBLK_MAX
-#define CH_WBLK_MAX 2048         // most strip workgroups per instance (larger grids loop over strips)
-#endif
                                  // <= 8 * CH_BLOCK partials per instance (sum_partials)
 #ifndef CH_LOOKAHEAD
 #define CH_LOOKAHEAD 2           // DCGS2 iterations the host issues ahead of the device's update launches
 #endif
 #define CH_LOOKAHEAD_WAIT_S 0.05 // longest host wait for that progress (then it issues anyway)
 #define CH_PLAN_WAIT_S 1.0       // longest host wait for the LIM orders a plan publishes (then it copies them)
-#ifndef CH_MARCH_L
-#define CH_MARCH_L 16            // planes per run of the 3-D marching matvec
-#endif
 #ifndef CH_CBLK_MAX
 #define CH_CBLK_MAX 512          // most streaming workgroups per instance
 #endif
@@ -88,9 +83,12 @@ struct Inst {
     int cblk0, cblk;    // streaming workgroups [cblk0, cblk0 + cblk)
     double eps2, inv_h2;
     int eyre;
-    int wblk0, wblk;    // 2-D row-strip / 3-D marching workgroups [wblk0, wblk0 + wblk)
+    int wblk0, wblk;    // partials of the 2-D row-strip / 3-D marching kernels [wblk0, wblk0 + wblk)
+    int zblk0, zblk;    // their workgroups [zblk0, zblk0 + zblk): one per partial where zgrp = 1
     int vx;             // 2-D strips: columns per lane (divides n)
-    int zlen;           // 3-D marching kernels: planes per run of a workgroup
+    int zlen;           // 3-D marching kernels: planes per run (of a partial)
+    int zgrp;           // ... and runs that a workgroup walks one after the other
+    int pld;            // row length of the reduction partials, the same for a whole table
     int bc;             // ch_bc
     int mob;            // variable mobility, coefficients in the control block
 };
@@ -138,8 +136,8 @@ struct DevBuffers {
     double* fcur;       // FP64 f(y^n) (start vector of the step, unnormalised)
     float* y32;         // FP32 copy of y^n (mixed precision only)
     double* zbuf;       // FP64 scratch (LIM stages)
-    double* part;       // reduction partials: two slots of CH_NRED * CH_MAXB
-    double* dots;       // DCGS2 dot-product partials: CH_DROWS rows of CH_MAXB
+    double* part;       // reduction partials: two slots of CH_NRED rows of Table::pld
+    double* dots;       // DCGS2 dot-product partials: CH_DROWS rows of Table::pld
     int* lorder;        // LIM node order, CH_PMAX per slot
     double* lcoef;      // LIM stage coefficients (tau a_m, 1 / (1 + tau a_m)) by stage position, 2 CH_PMAX per slot
     Ctl* ctl;           // control blocks, one per slot
@@ -169,6 +167,7 @@ struct Table {
     const int* wb2i;    // 2-D strip workgroup -> instance
     int ninst, sgrid, cgrid, dim;
     int wgrid;          // 2-D strip / 3-D marching workgroups
+    int pld;            // Inst::pld of its instances
     const Inst* hinst;  // host copy
 };
 
@@ -178,10 +177,11 @@ struct Table {
 // previous producer).  `stencil` records which workgroup ranges produced them.
 struct PartSeq {
     double* base = nullptr;
+    size_t ld = CH_MAXB;       // Table::pld of the launches
     int par = 0;
     int stencil = PK_STREAM;   // PartKind of the last producer
-    double* in() const { return base + (size_t)(par ^ 1) * CH_NRED * CH_MAXB; }
-    double* out() const { return base + (size_t)par * CH_NRED * CH_MAXB; }
+    double* in() const { return base + (size_t)(par ^ 1) * CH_NRED * ld; }
+    double* out() const { return base + (size_t)par * CH_NRED * ld; }
     void produced(int kind) {
         stencil = kind;
         par ^= 1;

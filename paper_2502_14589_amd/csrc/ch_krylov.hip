@@ -85,7 +85,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_mgs(Ctl* __restrict__ ctls, const 
         acc += FINAL ? double(w) * double(w) : double(w) * double(Vn[q]);
     }
     double x[1] = {acc};
-    write_partials<1, RED_SUM>(x, pout);
+    write_partials<1, RED_SUM>(x, pout, I.pld, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -399,7 +399,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_dots_reduce(Ctl* __restrict__ ctls
     if (ctl->done | ctl->halted) return;
     const int r = blockIdx.x;
     double tot[1];
-    sum_inst_partials<1, RED_SUM>(dots + (size_t)r * CH_MAXB, I, kind, tot);
+    sum_inst_partials<1, RED_SUM>(dots + (size_t)r * I.pld, I, kind, tot);
     if (threadIdx.x == 0) ctl->dt[r] = tot[0];
 }
 
@@ -850,7 +850,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_lim_begin(Ctl* __restrict__ ctls, 
         }
     }
     double x[3] = {-mn, mx, bad};
-    write_partials<3, RED_MAX>(x, pout);
+    write_partials<3, RED_MAX>(x, pout, I.pld, blockIdx.x);
 }
 
 // Order of the Chebyshev nodes beta_i = cos(pi (2i - 1) / (2p)) in a LIM
@@ -1357,7 +1357,7 @@ static std::vector<unsigned long long> graph_key(const Table& t, int prec, const
     p(b.phibig), p(b.part);
     const Inst& I = t.hinst[0];   // passed by value to single-instance launches
     v(I.off), v(I.N), v(I.n), v(I.slot), v(I.sblk0), v(I.sblk), v(I.cblk0), v(I.cblk), d(I.eps2), d(I.inv_h2);
-    v(I.eyre), v(I.wblk0), v(I.wblk), v(I.vx), v(I.bc), v(I.mob);
+    v(I.eyre), v(I.wblk0), v(I.wblk), v(I.zblk0), v(I.zblk), v(I.zlen), v(I.zgrp), v(I.pld), v(I.vx), v(I.bc), v(I.mob);
     return k;
 }
 

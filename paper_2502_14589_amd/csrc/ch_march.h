@@ -2,71 +2,7 @@
 #pragma once
 
 #include "ch_internal.h"
-
-// Rows (y) of the x-y block of a marching workgroup: 8 in FP64 (two x per
-// thread), 16 in FP32 (four x per thread); the block is 64 wide.
-constexpr int march_rows(int prec) { return prec == CH_FP64 ? 8 : 16; }
-
-// Planes per z-run of the FP32 DCGS2 matvec: of the lengths CH_MARCH_L ..
-// 2 CH_MARCH_L, the one whose work items (64 x 16 blocks times runs) fill the
-// largest share of whole rounds of co-resident workgroups, the shorter on
-// ties.  The kernel holds three workgroups per CU at its register count, so
-// 256 CUs hold 768: at 256^3 runs of 16 give 1024 items (a second round a
-// third full), runs of 22 give 768.  Only while every item has a workgroup
-// of its own at CH_MARCH_L (at most CH_WBLK_MAX items): beyond that the
-// workgroups loop over items, rounds no longer follow the item count, and
-// longer runs were slower (384^3, 512^3).
-constexpr unsigned MARCH_SLOTS_FP32 = 256u * 3u;
-
-inline int march_len_fp32(int n) {
-    const unsigned nxy = (unsigned)((n + 63) / 64) * (unsigned)((n + 15) / 16);
-    if ((unsigned long long)nxy * (unsigned)((n + CH_MARCH_L - 1) / CH_MARCH_L) > CH_WBLK_MAX) return CH_MARCH_L;
-    int best = CH_MARCH_L;
-    unsigned long long bi = 0, br = 1;   // items and rounds of the best length so far
-    for (int L = CH_MARCH_L; L <= 2 * CH_MARCH_L; ++L) {
-        const unsigned long long items = (unsigned long long)nxy * (unsigned)((n + L - 1) / L);
-        const unsigned long long rounds = (items + MARCH_SLOTS_FP32 - 1) / MARCH_SLOTS_FP32;
-        if (items * br > bi * rounds) {
-            best = L;
-            bi = items;
-            br = rounds;
-        }
-    }
-    return best;
-}
-
-// Planes per z-run of the FP64 kernels (matvec, estimate pass, LIM stage, LIM
-// estimate): 16 on large grids, down to 1 where 16 leave CUs without work.  A
-// plane step is a chain (a load, two stencil passes, the dot phase, a
-// barrier), so a grid that gives a CU one workgroup takes as long as its run:
-// 22 steps of 0.74 us in a LIM stage at L = 16, however small the grid.  More
-// workgroups on a CU share its time: a step of w of them takes about
-// 0.55 + 0.19 w of these units (w <= 4, the occupancy), so the length that
-// minimises L + 4 (the two planes on either side) times that, summed over the
-// rounds of workgroups, is taken, the longer on ties (fewer rim planes).
-// Measured, EE2 step of 30 iterations and LIM step of 38 passes, L = 16 and
-// the length picked: 32^3 1760 -> 690 us and 750 -> 330; 97^3 2409 -> 1669
-// and 826 -> 598 (L = 4); 128^3 3343 -> 3023 and 829 -> 695 (4); 192^3 9862 ->
-// 9550 and 1548 -> 1497 (8).  From 2048 workgroups at L = 16 on (256^3) every
-// shorter length was slower.
-inline int march_len_fp64(int n) {
-    const unsigned nxy = (unsigned)((n + 63) / 64) * (unsigned)((n + 7) / 8);
-    int best = CH_MARCH_L;
-    unsigned bt = ~0u;
-    for (int L = CH_MARCH_L; L >= 1; --L) {
-        const unsigned long long items = (unsigned long long)nxy * (unsigned)((n + L - 1) / L);
-        if (items > CH_WBLK_MAX) break;   // at CH_MARCH_L: the workgroups loop over items
-        const unsigned w = (unsigned)((items + 255) / 256), last = w % 4;
-        const unsigned t = (unsigned)(L + 4) * (w / 4 * 131 + (last ? 55 + 19 * last : 0));
-        if (t < bt) {
-            best = L;
-            bt = t;
-        }
-    }
-    return best;
-}
-
-inline int march_len(int n, int prec) { return prec == CH_FP64 ? march_len_fp64(n) : march_len_fp32(n); }
+#include "ch_runs.h"
 
 // 3-D estimate pass of EE2 on z-marching x-y tiles (ch_march.hip): f(y^{n+1})
 // into the field f and basis column 0 (and the FP32 copy of y^{n+1} in the

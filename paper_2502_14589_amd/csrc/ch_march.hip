@@ -10,7 +10,7 @@
 // <u, w>).
 //
 // Layout.  A workgroup owns an MX x MY block of (x, y) columns and a run of
-// zlen planes in z (march_len of the grid and the basis precision), which it
+// zlen planes in z (Inst::zlen; in a batch, zgrp such runs), which it
 // walks plane by plane.  Thread t owns the same
 // 16 bytes of consecutive-x columns of the block in every pass (the stencil
 // passes and the dot phase: two x in FP64, four in FP32), plus one column of
@@ -160,6 +160,31 @@ struct MarchItem {
     int x0, y0, z0, zl;
 };
 
+// Runs a workgroup walks one after the other, and the partial that each leaves.
+// A batch's workgroups walk I.zgrp runs of I.zlen planes without a stop (the two planes
+// on either side are then loaded once), and hand out each run's sums at its end:
+// run for run the sums of a single grid, whatever the group.
+template <bool SINGLE>
+struct MarchRuns {
+    int nxy, zlen, grp, nitems, lb;
+    __device__ __forceinline__ MarchRuns(const Inst& I, int nxy_) : nxy(nxy_), zlen(I.zlen), grp(SINGLE ? 1 : I.zgrp) {
+        const int nz = (I.n + zlen - 1) / zlen;
+        nitems = nxy * ((nz + grp - 1) / grp);
+        lb = xcd_remap(blockIdx.x - I.zblk0, I.zblk);
+    }
+    __device__ __forceinline__ int planes() const { return zlen * grp; }
+    // planes z0 .. zo of item `it` are done, zo the last of zl: a run of a group has ended
+    __device__ __forceinline__ bool ends(int zo, int z0, int zl) const {
+        return !SINGLE && grp > 1 && zo >= z0 && (zo + 1 == z0 + zl || (zo + 1 - z0) % zlen == 0);
+    }
+    // where the sums of the run that ends with plane zo go (groups), or those of the
+    // workgroup's items
+    __device__ __forceinline__ int at(const Inst& I, int it, int zo) const {
+        return I.wblk0 + xcd_unmap(zo / zlen * nxy + it % nxy, I.wblk);
+    }
+    __device__ __forceinline__ int at(const Inst& I) const { return I.wblk0 + (int)blockIdx.x - I.zblk0; }
+};
+
 template <int MX, int MY>
 __device__ __forceinline__ MarchItem march_item(int it, int n, int len) {
     const int ntx = (n + MX - 1) / MX, nty = (n + MY - 1) / MY;
@@ -228,9 +253,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_matvec_m(Ctl* __restrict__ ctls, c
     for (int i = tid; i < nrows * NW; i += CH_BLOCK) red[i / NW][i % NW] = 0.0;
     const int hv = wave_sum8_holder(lane);
     const int ntx = (n + MX - 1) / MX, nty = (n + MY - 1) / MY;
-    const int zlen = I.zlen;
-    const int nitems = ntx * nty * ((n + zlen - 1) / zlen);
-    const int lb = xcd_remap(blockIdx.x - I.wblk0, I.wblk);
+    const MarchRuns<SINGLE> R(I, ntx * nty);
     constexpr int RB = 4;   // columns per wave_sum8 (two sums each)
     // the thread's q points in the q region: its tile points, then its ring point
     // (lanes past the ring's end repeat its last point)
@@ -262,10 +285,21 @@ __global__ __launch_bounds__(CH_BLOCK) void k_matvec_m(Ctl* __restrict__ ctls, c
     // next planes (loads complete in issue order, so the dot phase then waits
     // for its columns but not for the prefetch)
     constexpr bool EARLY = sizeof(TV) == 8;
+    // the sums in `red` as the partials at position `pos`; the next run's start at zero
+    auto hand_out = [&](int pos) {
+        for (int i = tid; i < nrows; i += CH_BLOCK) {
+            double a = red[i][0];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) a += red[i][w];
+            pout[(size_t)i * I.pld + pos] = a;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) red[i][w] = 0.0;
+        }
+    };
     auto items = [&](auto vec_c) {
     constexpr bool VEC = decltype(vec_c)::value;
-    for (int it = lb; it < nitems; it += I.wblk) {
-        const MarchItem m = march_item<MX, MY>(it, n, zlen);
+    for (int it = R.lb; it < R.nitems; it += I.zblk) {
+        const MarchItem m = march_item<MX, MY>(it, n, R.planes());
         // byte offsets in a plane of the thread's operand-region values and
         // of its q points (periodic wrap; the region may extend past the
         // grid, whose outputs are masked below)
@@ -468,18 +502,18 @@ __global__ __launch_bounds__(CH_BLOCK) void k_matvec_m(Ctl* __restrict__ ctls, c
                 qm1[e] = qn[e];
             }
             __syncthreads();
+            if (R.ends(zo, z0, m.zl)) {
+                hand_out(R.at(I, it, zo));
+                __syncthreads();
+            }
         }
     }
     };
     if (DV == 1 || (DV == 2 && n % NPT == 0)) items(std::true_type{});
     else items(std::false_type{});
+    if (R.grp > 1) return;
     __syncthreads();
-    for (int i = tid; i < nrows; i += CH_BLOCK) {
-        double a = red[i][0];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) a += red[i][w];
-        pout[(size_t)i * CH_MAXB + blockIdx.x] = a;
-    }
+    hand_out(R.at(I));
 }
 
 
@@ -525,11 +559,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_est_m(Ctl* __restrict__ ctls, cons
     const double half_tau = 0.5 * (ctl->mode == MODE_EE ? ctl->tau_acc : ctl->tau_step);
     const int tid = threadIdx.x;
     const int ntx = (n + MX - 1) / MX, nty = (n + MY - 1) / MY;
-    // planes per run: the FP32 matvec's in the mixed form (its workgroup
-    // count is sized for them); from the host for a single grid
-    const int zlen = I.zlen;
-    const int nitems = ntx * nty * ((n + zlen - 1) / zlen);
-    const int lb = xcd_remap(blockIdx.x - I.wblk0, I.wblk);
+    const MarchRuns<SINGLE> R(I, ntx * nty);
     int qrx[NQL], qry[NQL];
     const int cx = NPT * (tid % TXT), cy = tid / TXT;
 #pragma unroll
@@ -556,10 +586,15 @@ __global__ __launch_bounds__(CH_BLOCK) void k_est_m(Ctl* __restrict__ ctls, cons
     }
     auto cc = [eyre](double v) { return 2.0 * v * v * v + (eyre ? v : 0.0); };
     double a_err = 0.0, a_pc = 0.0, a_f = 0.0, a_g = 0.0;
+    auto hand_out = [&](int pos) {
+        double x[4] = {a_err, a_pc, a_f, a_g};
+        write_partials<4, RED_SUM>(x, pout, I.pld, pos);
+        a_err = a_pc = a_f = a_g = 0.0;
+    };
     auto items = [&](auto vec_c) {
     constexpr bool VEC = decltype(vec_c)::value;
-    for (int it = lb; it < nitems; it += I.wblk) {
-        const MarchItem m = march_item<MX, MY>(it, n, zlen);
+    for (int it = R.lb; it < R.nitems; it += I.zblk) {
+        const MarchItem m = march_item<MX, MY>(it, n, R.planes());
         unsigned vo[NVL], qpos[NQL];
 #pragma unroll
         for (int l = 0; l < NVL; ++l) {
@@ -712,13 +747,13 @@ __global__ __launch_bounds__(CH_BLOCK) void k_est_m(Ctl* __restrict__ ctls, cons
 #pragma unroll
             for (int l = 0; l < NQL; ++l) vm[l] = vc[l];
             __syncthreads();
+            if (R.ends(zo, z0, m.zl)) hand_out(R.at(I, it, zo));
         }
     }
     };
     if (DV == 1 || (DV == 2 && n % NPT == 0)) items(std::true_type{});
     else items(std::false_type{});
-    double x[4] = {a_err, a_pc, a_f, a_g};
-    write_partials<4, RED_SUM>(x, pout);
+    if (R.grp == 1) hand_out(R.at(I));
 }
 
 
@@ -761,9 +796,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_lim_stage_m(Ctl* __restrict__ ctls
     const double ta = cf[0], inv = cf[1];
     const int tid = threadIdx.x;
     const int ntx = (n + MX - 1) / MX, nty = (n + MY - 1) / MY;
-    const int zlen = I.zlen;
-    const int nitems = ntx * nty * ((n + zlen - 1) / zlen);
-    const int lb = xcd_remap(blockIdx.x - I.wblk0, I.wblk);
+    const MarchRuns<SINGLE> R(I, ntx * nty);
     int qrx[NQL], qry[NQL];
     const int cx = NPT * (tid % TXT), cy = tid / TXT;
 #pragma unroll
@@ -790,8 +823,8 @@ __global__ __launch_bounds__(CH_BLOCK) void k_lim_stage_m(Ctl* __restrict__ ctls
     }
     auto items = [&](auto vec_c) {
     constexpr bool VEC = decltype(vec_c)::value;
-    for (int it = lb; it < nitems; it += I.wblk) {
-        const MarchItem m = march_item<MX, MY>(it, n, zlen);
+    for (int it = R.lb; it < R.nitems; it += I.zblk) {
+        const MarchItem m = march_item<MX, MY>(it, n, R.planes());
         unsigned vo[NVL], qpos[NQL];
 #pragma unroll
         for (int q = 0; q < NVL; ++q) {
@@ -963,9 +996,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_est_lim_m(Ctl* __restrict__ ctls, 
     const double half_tau = 0.5 * ctl->tau0;
     const int tid = threadIdx.x;
     const int ntx = (n + MX - 1) / MX, nty = (n + MY - 1) / MY;
-    const int zlen = I.zlen;
-    const int nitems = ntx * nty * ((n + zlen - 1) / zlen);
-    const int lb = xcd_remap(blockIdx.x - I.wblk0, I.wblk);
+    const MarchRuns<SINGLE> R(I, ntx * nty);
     int qrx[NQL], qry[NQL];
     const int cx = NPT * (tid % TXT), cy = tid / TXT;
 #pragma unroll
@@ -991,11 +1022,16 @@ __global__ __launch_bounds__(CH_BLOCK) void k_est_lim_m(Ctl* __restrict__ ctls, 
         }
     }
     double a_err = 0.0, a_pc = 0.0;
+    auto hand_out = [&](int pos) {
+        double x[2] = {a_err, a_pc};
+        write_partials<2, RED_SUM>(x, pout, I.pld, pos);
+        a_err = a_pc = 0.0;
+    };
     auto items = [&](auto vec_c) {
     constexpr bool VEC = decltype(vec_c)::value;
     (void)VEC;
-    for (int it = lb; it < nitems; it += I.wblk) {
-        const MarchItem m = march_item<MX, MY>(it, n, zlen);
+    for (int it = R.lb; it < R.nitems; it += I.zblk) {
+        const MarchItem m = march_item<MX, MY>(it, n, R.planes());
         unsigned vo[NVL], qpos[NQL];
 #pragma unroll
         for (int q = 0; q < NVL; ++q) {
@@ -1137,13 +1173,13 @@ __global__ __launch_bounds__(CH_BLOCK) void k_est_lim_m(Ctl* __restrict__ ctls, 
 #pragma unroll
             for (int q = 0; q < NQL; ++q) sm[q] = vc[q];
             __syncthreads();
+            if (R.ends(p - 1, z0, m.zl)) hand_out(R.at(I, it, p - 1));
         }
     }
     };
     if (DV == 1 || (DV == 2 && n % NPT == 0)) items(std::true_type{});
     else items(std::false_type{});
-    double x[2] = {a_err, a_pc};
-    write_partials<2, RED_SUM>(x, pout);
+    if (R.grp == 1) hand_out(R.at(I));
 }
 
 }  // namespace

@@ -198,11 +198,11 @@ __global__ __launch_bounds__(CH_BLOCK) void k_matvec(Ctl* __restrict__ ctls, con
             double a = red[i][0];
 #pragma unroll
             for (int w = 1; w < NW; ++w) a += red[i][w];
-            pout[(size_t)i * CH_MAXB + blockIdx.x] = a;
+            pout[(size_t)i * I.pld + blockIdx.x] = a;
         }
     } else {
         double x[1] = {dot};
-        write_partials<1, RED_SUM>(x, pout);
+        write_partials<1, RED_SUM>(x, pout, I.pld, blockIdx.x);
     }
 }
 
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_resid(Ctl* __restrict__ ctls, cons
         __syncthreads();
     }
     double x[2] = {acc_r, acc_g};
-    write_partials<2, RED_SUM>(x, pout);
+    write_partials<2, RED_SUM>(x, pout, I.pld, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(CH_BLOCK) void k_est_lim(Ctl* __restrict__ ctls, co
         __syncthreads();
     }
     double x[2] = {a_err, a_pc};
-    write_partials<2, RED_SUM>(x, pout);
+    write_partials<2, RED_SUM>(x, pout, I.pld, blockIdx.x);
 }
 
 }  // namespace

@@ -202,11 +202,11 @@ __global__ __launch_bounds__(CH_STRIP_BLOCK) void k_matvec_s(Ctl* __restrict__ c
             double t = red[i][0];
 #pragma unroll
             for (int x = 1; x < W; ++x) t += red[i][x];
-            pout[(size_t)i * CH_MAXB + blockIdx.x] = t;
+            pout[(size_t)i * I.pld + blockIdx.x] = t;
         }
     } else {
         double x[1] = {one};
-        write_partials<1, RED_SUM>(x, pout);
+        write_partials<1, RED_SUM>(x, pout, I.pld, blockIdx.x);
     }
 }
 
@@ -555,7 +555,7 @@ __global__ __launch_bounds__(CH_STRIP_BLOCK) void k_est_ee_s(Ctl* __restrict__ c
         else if (sizeof(TV) == 8 || I.vx == 2) est_strips<TV, 2, false, false>(I, y0base, y1base, fbase, V0base, y32base, half_tau, wv, acc, Mob{});
         else est_strips<TV, (sizeof(TV) == 4 ? 4 : 2), false, false>(I, y0base, y1base, fbase, V0base, y32base, half_tau, wv, acc, Mob{});
     }
-    write_partials<4, RED_SUM>(acc, pout);
+    write_partials<4, RED_SUM>(acc, pout, I.pld, blockIdx.x);
 }
 
 }  // namespace
