@@ -490,6 +490,7 @@ int build_table(ch_ctx* ctx, const std::vector<Member>& ms, int dim, int prec, T
             I.vx = sp->vx;
             I.wblk = sp->wblk;
             I.cblk = sp->cblk;
+            if (dim == 3) I.zlen = march_len_set(I.n, prec, I.wblk);
         } else {
             built_in[i] = march64;
         }

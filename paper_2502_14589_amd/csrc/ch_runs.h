@@ -79,6 +79,18 @@ inline int march_len_fp64(int n) {
 
 inline int march_len(int n, int prec) { return prec == CH_FP64 ? march_len_fp64(n) : march_len_fp32(n); }
 
+// ... and under a launch shape of `wblk` workgroups: the shortest runs from that
+// length on that give every workgroup one run, CH_MARCH_L where none does (the workgroups
+// then loop over runs, and the short ones cost two planes on either side each:
+// 32^3 with 8 workgroups, two steps 1830 us EE2 and 1420 LIM with runs of 16, 2950 and 4090 with runs of 1).
+inline int march_len_set(int n, int prec, int wblk) {
+    int L = march_len(n, prec);
+    if (prec != CH_FP64) return L;
+    const long long nxy = (long long)((n + 63) / 64) * ((n + 7) / 8);
+    while (L < CH_MARCH_L && nxy * ((n + L - 1) / L) > wblk) ++L;
+    return L;
+}
+
 // Workgroups of a grid whose workgroups walk `grp` runs each.
 inline int march_groups(int n, int zlen, int grp) {
     return ((n + 63) / 64) * ((n + 7) / 8) * (((n + zlen - 1) / zlen + grp - 1) / grp);

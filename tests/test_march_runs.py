@@ -22,6 +22,9 @@ int main() {
             }
         std::printf("\n");
     }
+    std::printf("set\n");
+    for (int n = 5; n <= 420; ++n)
+        for (int w : {1, 3, 8, 20, 64, 200, 700, 2048}) std::printf("%d %d %d %d\n", n, w, march_len(n, CH_FP64), march_len_set(n, CH_FP64, w));
 }
 """
 
@@ -34,7 +37,7 @@ def rows(tmp_path_factory):
     (d / "runs.cpp").write_text(PROGRAM)
     subprocess.run(["g++", "-std=c++17", "-I", CSRC, str(d / "runs.cpp"), "-o", str(d / "runs")], check=True)
     out = subprocess.run([str(d / "runs")], capture_output=True, text=True, check=True).stdout
-    return [[int(x) for x in line.split()] for line in out.splitlines()]
+    return [[[int(x) for x in line.split()] for line in part.splitlines()] for part in out.split("set\n")]
 
 
 def ceil(a, b):
@@ -42,7 +45,7 @@ def ceil(a, b):
 
 
 def test_groups_cover_every_run(rows):
-    for n, L, *rest in rows:
+    for n, L, *rest in rows[0]:
         nxy, runs = ceil(n, 64) * ceil(n, 8), ceil(n, L)
         assert 1 <= L <= 16
         for g, groups in zip(rest[::2], rest[1::2]):
@@ -52,6 +55,14 @@ def test_groups_cover_every_run(rows):
 
 def test_batches_that_runs_of_16_allow_stay_allowed(rows):
     """Members of built-in shape count by their stencil tiles (at most 2048): never fewer than their runs of 16 planes."""
-    for n, *_ in rows:
+    for n, *_ in rows[0]:
         tiles = min(ceil(n, 32) * ceil(n, 4) ** 2, 2048)
         assert min(ceil(n, 64) * ceil(n, 8) * ceil(n, 16), 2048) <= tiles
+
+
+def test_runs_of_a_set_shape(rows):
+    """Fewer workgroups than built in get longer runs, one each, and 16 planes where they have to loop over runs."""
+    for n, w, built_in, L in rows[1]:
+        items = lambda planes: ceil(n, 64) * ceil(n, 8) * ceil(n, planes)   # noqa: E731
+        fits = [x for x in range(built_in, 17) if items(x) <= w]
+        assert L == (fits[0] if fits else 16)
