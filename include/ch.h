@@ -366,6 +366,26 @@ int ch_time_kernel(ch_ctx *ctx, const ch_problem *prob, int kernel, int m_max, c
                    double *total_us, double *total_bytes);
 
 /*
+ * Resident launches.  ch_run_ee, ch_step_ee, ch_phiv, ch_run_lim and ch_step_lim issue a whole
+ * Krylov cycle, or all stages of a LIM step, of a single 2-D grid that fits the device as
+ * one launch whose workgroups wait for each other.  Every wait is bounded: when one
+ * runs out (the workgroups did not fit beside what else runs on the device), the launch ends and the
+ * step is repeated with ordinary launches; the results are the same.
+ *
+ * ch_set_resident: enabled 0 keeps the context to ordinary launches.  wait_us: the
+ * longest wait in microseconds (0 .. 10^7; < 0: the built-in 500000; a new context takes it from the
+ * environment variable CH_RESIDENT_WAIT_US where that is set).  after: the context's next `after`
+ * resident launches still have the bound before.  ch_get_resident: the context's counts.
+ */
+typedef struct {
+    long long launches;   /* resident launches issued */
+    long long repeats;    /* those a wait of which ran out */
+} ch_resident_info;
+
+int ch_set_resident(ch_ctx *ctx, int enabled, int wait_us, int after);
+int ch_get_resident(ch_ctx *ctx, ch_resident_info *out);
+
+/*
  * Launch shape of one grid (dim, n, precision); the same for every instance of
  * that grid in single runs, batches and served requests on the context:
  *   vx    2-D: grid columns per lane of the row-strip kernels (1, 2, or 4 in

@@ -27,7 +27,7 @@ EXPORTED = (
     "ch_create", "ch_destroy", "ch_strerror", "ch_last_error_message",
     "ch_run_ee", "ch_step_ee", "ch_run_ee_batch", "ch_run_lim", "ch_run_lim_batch", "ch_step_lim", "ch_step_lim_noalloc", "ch_phiv",
     "ch_time_kernel", "ch_get_shape", "ch_set_shape", "ch_tune_shape", "ch_tune_batch_shapes",
-
+    "ch_set_resident", "ch_get_resident",
     "ch_server_create", "ch_server_destroy", "ch_submit", "ch_poll",
 )
 CH_REQ_QUEUED, CH_REQ_RUNNING, CH_REQ_DONE, CH_REQ_FAILED = 0, 1, 2, 3
@@ -76,6 +76,13 @@ class ChBatchItem(ctypes.Structure):
 class ChRequest(ctypes.Structure):
     _fields_ = [("n", c_int), ("eps", c_double), ("y0", c_void_p), ("steps", c_int), ("tau0", c_double),
                 ("method", c_int), ("T", c_double), ("tol", c_double), ("y0_on_host", c_int)]
+
+
+class ChResidentInfo(ctypes.Structure):
+    _fields_ = [("launches", c_longlong), ("repeats", c_longlong)]
+
+    def as_dict(self):
+        return {name: getattr(self, name) for name, _ in self._fields_}
 
 
 class ChError(RuntimeError):
@@ -127,9 +134,12 @@ def load_library(path: str = LIB_PATH):
     lib.ch_tune_shape.argtypes = [c_void_p, P(ChProblem), c_int, P(ChShape), P(c_double), P(c_double)]
     lib.ch_tune_batch_shapes.argtypes = [c_void_p, c_int, P(ChBatchItem), c_int, c_int, c_int, c_int, P(c_double),
                                          P(c_double)]
+    lib.ch_set_resident.argtypes = [c_void_p, c_int, c_int, c_int]
+    lib.ch_get_resident.argtypes = [c_void_p, P(ChResidentInfo)]
     for name in ("ch_create", "ch_destroy", "ch_run_ee", "ch_step_ee", "ch_run_ee_batch", "ch_run_lim", "ch_run_lim_batch",
                  "ch_step_lim", "ch_step_lim_noalloc", "ch_phiv", "ch_time_kernel", "ch_server_create", "ch_server_destroy", "ch_submit",
-                 "ch_poll", "ch_get_shape", "ch_set_shape", "ch_tune_shape", "ch_tune_batch_shapes"):
+                 "ch_poll", "ch_get_shape", "ch_set_shape", "ch_tune_shape", "ch_tune_batch_shapes", "ch_set_resident",
+                 "ch_get_resident"):
         getattr(lib, name).restype = c_int
     _lib = lib
     return lib
@@ -345,6 +355,18 @@ class Context:
         rc = self.lib.ch_time_kernel(self._ptr, byref(pb), int(kernel), int(m_max), arr, n, byref(us), byref(by))
         self._raise(rc, "ch_time_kernel")
         return us.value, by.value
+
+    # -- resident launches ---------------------------------------------------
+    def set_resident(self, enabled: bool = True, wait_us: int = -1, after: int = 0):
+        """Resident launches of this context: on or off, their longest wait (< 0: built in) and how many of
+        them still take the wait set before."""
+        self._raise(self.lib.ch_set_resident(self._ptr, int(bool(enabled)), int(wait_us), int(after)), "ch_set_resident")
+
+    def resident_info(self) -> dict:
+        """{'launches': resident launches issued, 'repeats': those that gave up waiting}."""
+        out = ChResidentInfo()
+        self._raise(self.lib.ch_get_resident(self._ptr, byref(out)), "ch_get_resident")
+        return out.as_dict()
 
     # -- launch shapes -------------------------------------------------------
     def get_shape(self, dim: int, n: int, precision: int = CH_FP64) -> dict:

@@ -51,6 +51,12 @@ struct ch_ctx {
     int part_ld = 0, dots_ld = 0;   // row lengths b.part and b.dots have room for
     int cus = 0;             // compute units of the device
     int epoch = 0;           // last flag value given to a resident launch
+    struct {
+        bool on = true;      // ch_set_resident
+        unsigned wait_us = CH_RES_WAIT_US;   // the wait bound of the launches after the next `after`
+        int after = 0;
+        long long launches = 0, repeats = 0;
+    } res;
     CycleShape cyc{0, 0};    // resident Krylov cycles of the current call (strips = 0: ordinary launches)
     int phibig_slots = 0;    // slots of the phi scratch of orders above 48
     ch_step_record* rec = nullptr;
@@ -343,8 +349,11 @@ int ensure_resident(ch_ctx* ctx, bool cycle) {
 }
 
 // The epoch of a resident launch that uses `count` values above it (the
-// words start over long before an int overflows).
-int next_epoch(ch_ctx* ctx, int count, int* epoch) {
+// words start over long before an int overflows), and its wait bound.
+int next_resident(ch_ctx* ctx, int count, int* epoch) {
+    ctx->res.launches += 1;
+    if (ctx->res.after > 0) ctx->res.after -= 1;
+    else ctx->b.wait_us = ctx->res.wait_us;
     if (ctx->epoch > (1 << 30)) {
         HIP_TRY(ctx, hipMemsetAsync(ctx->b.flags, 0, sizeof(int) * CH_RES_WORDS, ctx->stream));
         ctx->epoch = 1;
@@ -615,7 +624,7 @@ bool all_halted(const ch_ctx* ctx, int n) {
 int issue_cycle(ch_ctx* ctx, const Table& t, int prec, PartSeq& ps, const double* y, int m_max, int orth) {
     if (ctx->cyc.strips > 0) {
         int epoch, rc;
-        if ((rc = next_epoch(ctx, CYCLE_EPOCHS, &epoch))) return rc;
+        if ((rc = next_resident(ctx, CYCLE_EPOCHS, &epoch))) return rc;
         HIP_TRY(ctx, launch_cycle(t, prec, ctx->b, ctx->cyc, epoch, y, m_max, ctx->stream));
         return CH_OK;
     }
@@ -627,7 +636,7 @@ int issue_cycle(ch_ctx* ctx, const Table& t, int prec, PartSeq& ps, const double
 // lease is held until the call returns.
 void use_resident_cycles(ch_ctx* ctx, const Table& t, int m_max, int orth, int graph_chunk, ResidentLease* lease) {
     ctx->cyc = CycleShape{0, 0};
-    if (orth != CH_ORTH_DCGS2 || graph_chunk > 0) return;
+    if (!ctx->res.on || orth != CH_ORTH_DCGS2 || graph_chunk > 0) return;
     const CycleShape c = cycle_shape(t, m_max, ctx->cus);
     if (c.strips > 0 && ensure_resident(ctx, true) == CH_OK && lease->take(ctx->device, ctx->cus, c.workgroups)) ctx->cyc = c;
 }
@@ -639,6 +648,7 @@ bool resident_retry(ch_ctx* ctx, int* rc) {
     *rc = CH_OK;
     if (h.status != CH_RES_RETRY) return false;
     ctx->cyc = CycleShape{0, 0};
+    ctx->res.repeats += 1;
     h.status = CH_OK;
     h.halted = 0;
     h.restarts -= h.cycles - 1;   // those of the unfinished step, which begins again
@@ -996,7 +1006,7 @@ int issue_lim_resident(ch_ctx* ctx, const Table& t, const LimTiles& g, PartSeq& 
         HIP_TRY(ctx, launch_lim_begin(t, b, ps, yin, ctx->stream));
         HIP_TRY(ctx, launch_lim_plan(t, b, ps, ++ctx->lseq, ctx->stream));
         int epoch;
-        if ((rc = next_epoch(ctx, LIM_EPOCHS, &epoch))) return rc;
+        if ((rc = next_resident(ctx, LIM_EPOCHS, &epoch))) return rc;
         HIP_TRY(ctx, launch_lim_run(t, b, g, epoch, yin, yout, ctx->stream));
         HIP_TRY(ctx, launch_est_lim(t, b, ps, yin, yout, ctx->stream));
         HIP_TRY(ctx, launch_lim_end(t, b, ps, ctx->stream));
@@ -1005,6 +1015,7 @@ int issue_lim_resident(ch_ctx* ctx, const Table& t, const LimTiles& g, PartSeq& 
     *s = h.steps;
     *done = h.status != CH_RES_RETRY;
     if (*done) return CH_OK;
+    ctx->res.repeats += 1;
     h.status = CH_OK;
     h.halted = 0;
     HIP_TRY(ctx, hipMemcpyAsync(b.ctl, &h, CTL_HEAD, hipMemcpyHostToDevice, ctx->stream));
@@ -1033,7 +1044,7 @@ int run_lim(ch_ctx* ctx, const ch_problem* prob, double* y, double tau0, double 
     long long s0 = 0;
     bool done = false;
     ResidentLease lease;   // held until the call returns: its stream has drained then
-    if (uses_strips(t)) {
+    if (ctx->res.on && uses_strips(t)) {
         const LimTiles g = lim_tiles(t.hinst[0], ctx->cus);
         if (g.rows > 0 && ensure_resident(ctx, false) == CH_OK && lease.take(ctx->device, ctx->cus, g.ntx * g.nty)) {
             if ((rc = issue_lim_resident(ctx, t, g, ps, max_steps, &s0, &done))) return rc;
@@ -1499,7 +1510,8 @@ int ch_create(ch_ctx** out, int device, void* hip_stream) {
     // CH_RESIDENT_WAIT_US: how long a workgroup of a resident launch waits for
     // another before the step is repeated with ordinary launches
     const char* w = getenv("CH_RESIDENT_WAIT_US");
-    ctx->b.wait_us = w ? (unsigned)std::max(0l, std::min(strtol(w, nullptr, 10), 10000000l)) : CH_RES_WAIT_US;
+    if (w) ctx->res.wait_us = (unsigned)std::max(0l, std::min(strtol(w, nullptr, 10), (long)CH_RES_WAIT_MAX_US));
+    ctx->b.wait_us = ctx->res.wait_us;
     noalloc_setup(device);
     LaunchEnv& sd = ctx->env;
     sd.graphs = &ctx->graphs;
@@ -1559,6 +1571,21 @@ const char* ch_strerror(int status) {
 }
 
 const char* ch_last_error_message(ch_ctx* ctx) { return ctx ? ctx->err.c_str() : ""; }
+
+int ch_set_resident(ch_ctx* ctx, int enabled, int wait_us, int after) {
+    if (!ctx || wait_us > CH_RES_WAIT_MAX_US || after < 0) return CH_EINVAL;
+    ctx->res.on = enabled != 0;
+    ctx->res.wait_us = wait_us < 0 ? CH_RES_WAIT_US : (unsigned)wait_us;
+    ctx->res.after = after;
+    return CH_OK;
+}
+
+int ch_get_resident(ch_ctx* ctx, ch_resident_info* out) {
+    if (!ctx || !out) return CH_EINVAL;
+    out->launches = ctx->res.launches;
+    out->repeats = ctx->res.repeats;
+    return CH_OK;
+}
 
 int ch_run_ee(ch_ctx* ctx, const ch_problem* prob, double* y, double tau0, double t0, double T, int max_steps,
               const ch_ee_opts* opts, ch_run_stats* stats, ch_step_record* records) {

@@ -35,6 +35,7 @@
 // when a wait ran out: never returned to a caller.
 #define CH_RES_RETRY 1000
 #define CH_RES_WAIT_US 500000
+#define CH_RES_WAIT_MAX_US 10000000
 
 #ifdef __HIPCC__
 namespace {

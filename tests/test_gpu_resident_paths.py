@@ -1,0 +1,100 @@
+"""Which launches a call takes: the counts of the context say which path ran, and a context kept to
+ordinary launches is the reference.  Their results agree bit for bit.
+"""
+import threading
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2502_14589_amd import ch
+from paper_2502_14589_amd.inputs import uniform_field
+
+
+def say(msg):
+    print(msg, flush=True)
+
+
+def dev(y):
+    import torch
+
+    return torch.from_numpy(np.ascontiguousarray(y, dtype=np.float64)).to("cuda")
+
+
+def problem(n, kind, prec=ch.CH_FP64):
+    length = 64.0 if kind == "neumann" else 1.0
+    bc = ch.CH_BC_NEUMANN if kind == "neumann" else ch.CH_BC_PERIODIC
+    p = ch.Problem(2, n, 3.0 * length / n, precision=prec, bc=bc, length=length, mobility=(0.1, 1.0) if kind == "mobility" else None)
+    return p, p.eps ** 2 * 64.0 * (n / length) ** 4
+
+
+def call(c, what, p, rho, y0):
+    """One call; its field, statistics and records.  Adaptive steps, restarted constant steps, LIM, the phi action."""
+    y = dev(y0)
+    if what == "ee":
+        st, recs = c.run_ee(p, y, 400.0 / rho, max_steps=6, m_max=20, records=True)
+    elif what == "constant":
+        st, recs = c.run_ee(p, y, 60.0 / rho, max_steps=3, m_max=8, tol_phi_fixed=1e-6, constant_step=True, records=True)
+    elif what == "lim":
+        st, recs = c.run_lim(p, y, 600.0 / rho, max_steps=4, records=True)
+    else:
+        z = dev(y0)
+        st, recs = c.phiv(p, y, z, 300.0 / rho, mode=ch.CH_PHI_RESTART if what == "phiv" else ch.CH_PHI_SHRINK, m_max=8), None
+        y = z
+    return y.cpu().numpy(), st, recs
+
+
+CALLS = ["ee", "constant", "lim", "phiv", "shrink"]
+
+
+@pytest.mark.parametrize("what", CALLS)
+@pytest.mark.parametrize("n,kind,prec", [(13, "periodic", ch.CH_FP64), (96, "neumann", ch.CH_FP64), (125, "mobility", ch.CH_FP64),
+                                         (96, "periodic", ch.CH_FP32_MIXED)])
+def test_resident_against_ordinary_launches(n, kind, prec, what):
+    """The counts tell the paths apart; the results do not."""
+    say(f"paths of {what} n={n} {kind} prec={prec}")
+    p, rho = problem(n, kind, prec)
+    y0 = uniform_field(n, 2, 0.1, 0.4, seed=8800 + n)
+    with ch.Context(0) as c, ch.Context(0) as o:
+        o.set_resident(False)
+        got, ref = call(c, what, p, rho, y0), call(o, what, p, rho, y0)
+        info = c.resident_info()
+        assert info["launches"] >= 1 and info["repeats"] == 0
+        assert o.resident_info() == {"launches": 0, "repeats": 0}
+    assert got[1:] == ref[1:] and np.array_equal(got[0], ref[0])
+
+
+@pytest.mark.parametrize("n", [96, 640])
+def test_launches_of_several_streams_share_the_device(n):
+    """Contexts of three threads, each on a stream of its own: at 96^2 their launches fit the device together, at 640^2
+    some are refused the room and take the ordinary form.  No wait runs out, and all give the result of a run alone."""
+    import torch
+
+    say(f"three streams n={n}")
+    p, rho = problem(n, "periodic")
+    y0 = uniform_field(n, 2, 0.1, 0.4, seed=8950)
+    with ch.Context(0) as o:
+        o.set_resident(False)
+        ref = [call(o, what, p, rho, y0) for what in ("ee", "lim")]
+    got, infos, errors = [None] * 3, [None] * 3, []
+
+    def work(i):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                with ch.Context(0) as c:
+                    for _ in range(8):
+                        got[i] = [call(c, what, p, rho, y0) for what in ("ee", "lim")]
+                        for g, r in zip(got[i], ref):
+                            assert g[1:] == r[1:] and np.array_equal(g[0], r[0])
+                    infos[i] = c.resident_info()
+        except Exception as e:   # reported by the main thread
+            errors.append(e)
+
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(3)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not errors, errors
+    assert sum(x["launches"] for x in infos) > 0 and sum(x["repeats"] for x in infos) == 0
