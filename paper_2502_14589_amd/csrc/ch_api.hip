@@ -641,20 +641,35 @@ void use_resident_cycles(ch_ctx* ctx, const Table& t, int m_max, int orth, int g
     if (c.strips > 0 && ensure_resident(ctx, true) == CH_OK && lease->take(ctx->device, ctx->cus, c.workgroups)) ctx->cyc = c;
 }
 
-// After read_heads: true when a resident cycle gave up waiting.  The run then
-// goes on from the last accepted state with ordinary launches.
-bool resident_retry(ch_ctx* ctx, int* rc) {
+// After read_heads: true when a resident cycle gave up waiting.  The call goes on
+// with ordinary launches: the control block is again as that cycle began (under
+// a new count, which no flag of the interrupted launch matches), and repeat_cycle starts it.
+bool resident_expired(ch_ctx* ctx, int* rc) {
     Ctl& h = ctx->hctl[0];
     *rc = CH_OK;
     if (h.status != CH_RES_RETRY) return false;
     ctx->cyc = CycleShape{0, 0};
     ctx->res.repeats += 1;
     h.status = CH_OK;
-    h.halted = 0;
-    h.restarts -= h.cycles - 1;   // those of the unfinished step, which begins again
+    h.halted = h.done = h.j = h.converged = h.traced = 0;
+    h.cyc += 1;
     ctx->expect[0] = h.cyc;
     if (hipMemcpyAsync(ctx->b.ctl, &h, CTL_HEAD, hipMemcpyHostToDevice, ctx->stream) != hipSuccess) *rc = CH_EDEVICE;
     return true;
+}
+
+// The start vector of the cycle that resident_expired has put back, from the same bits
+// as before: f(y^n) as kept for the first cycle of an EE2 step (its norm and tolerance are still in
+// the control block), the residual at the sub-step state z (at y for a first cycle) otherwise.
+int repeat_cycle(ch_ctx* ctx, const Table& t, int prec, PartSeq& ps, const double* y, const double* z) {
+    const Ctl& h = ctx->hctl[0];
+    if (h.cycles == 1 && h.mode != MODE_PHI) {
+        HIP_TRY(ctx, launch_start_vector(t, prec, ctx->b, ctx->stream));
+        return CH_OK;
+    }
+    HIP_TRY(ctx, launch_resid(t, prec, ctx->b, ps, y, h.cycles == 1 ? y : z, false, false, ctx->stream));
+    HIP_TRY(ctx, launch_after_resid(t, ctx->b, ps, false, ctx->stream));
+    return CH_OK;
 }
 
 // Remaining Krylov cycles of a constant step of one instance (linear RT
@@ -668,13 +683,19 @@ int restart_cycles(ch_ctx* ctx, const Table& t, int prec, PartSeq& ps, const dou
         int rc = read_heads(ctx, 1);
         if (rc) return rc;
         const Ctl& h = ctx->hctl[0];
-        if (h.halted || h.converged) return CH_OK;
-        HIP_TRY(ctx, launch_cycle_begin(t, b, ctx->stream));
-        ctx->expect[t.hinst[0].slot] += 1;
-        HIP_TRY(ctx, launch_resid(t, prec, b, ps, y, z, false, false, ctx->stream));
-        HIP_TRY(ctx, launch_after_resid(t, b, ps, false, ctx->stream));
+        const double* from = z;
+        if (resident_expired(ctx, &rc)) {
+            if (rc || (rc = repeat_cycle(ctx, t, prec, ps, y, z))) return rc;
+            if (h.cycles == 1) from = y;
+        } else {
+            if (h.halted || h.converged) return CH_OK;
+            HIP_TRY(ctx, launch_cycle_begin(t, b, ctx->stream));
+            ctx->expect[t.hinst[0].slot] += 1;
+            HIP_TRY(ctx, launch_resid(t, prec, b, ps, y, z, false, false, ctx->stream));
+            HIP_TRY(ctx, launch_after_resid(t, b, ps, false, ctx->stream));
+        }
         if ((rc = issue_cycle(ctx, t, prec, ps, y, m_max, orth))) return rc;
-        HIP_TRY(ctx, launch_update(t, prec, b, z, z, orth == CH_ORTH_DCGS2, ctx->stream));
+        HIP_TRY(ctx, launch_update(t, prec, b, from, z, orth == CH_ORTH_DCGS2, ctx->stream));
     }
     ctx->err = "restart cycle limit reached";
     return CH_ETAU_UNDERFLOW;
@@ -692,19 +713,23 @@ void fill_stats(const Ctl& h, ch_run_stats* st) {
 }
 
 // Issue EE2 steps for every instance of the table until all are halted (each
-// stops at its own T or step limit) or `max_launch` steps have been issued,
-// the first `done` of them before this call.
+// stops at its own T or step limit) or `max_launch` steps have been issued.
+// resume (one instance): go on with the first cycle of step `done`, which
+// resident_expired has put back.
 bool graph_chunk_ok(const ch_ee_opts* o) { return o->graph_chunk >= 0 && o->graph_chunk <= CH_MMAX + 1; }
 
 int issue_ee_steps(ch_ctx* ctx, const Table& t, int prec, int m_max, int orth, bool constant, long long max_launch,
-                   long long done = 0) {
+                   bool resume = false, long long done = 0) {
     const DevBuffers& b = ctx->b;
     PartSeq ps = partials_of(b, t);
     int rc;
-    const double* y0 = b.ybuf[done & 1];
-    HIP_TRY(ctx, launch_resid(t, prec, b, ps, y0, y0, true, true, ctx->stream));
-    HIP_TRY(ctx, launch_after_resid(t, b, ps, true, ctx->stream));
-    for (int i = 0; i < t.ninst; ++i) ctx->expect[t.hinst[i].slot] += 1;
+    if (resume) {
+        if ((rc = repeat_cycle(ctx, t, prec, ps, b.ybuf[done & 1], b.ybuf[(done & 1) ^ 1]))) return rc;
+    } else {
+        HIP_TRY(ctx, launch_resid(t, prec, b, ps, b.ybuf[0], b.ybuf[0], true, true, ctx->stream));
+        HIP_TRY(ctx, launch_after_resid(t, b, ps, true, ctx->stream));
+        for (int i = 0; i < t.ninst; ++i) ctx->expect[t.hinst[i].slot] += 1;
+    }
     for (long long s = done; s < max_launch; ++s) {
         const int p = (int)(s & 1);
         if ((rc = issue_cycle(ctx, t, prec, ps, b.ybuf[p], m_max, orth))) return rc;
@@ -839,16 +864,15 @@ int run_ee(ch_ctx* ctx, const ch_problem* prob, double* y, double tau0, double t
     const long long limit = max_steps > 0 ? max_steps : (1LL << 40);
     ResidentLease lease;
     use_resident_cycles(ctx, t, opts->m_max, opts->orth, opts->graph_chunk, &lease);
-    long long done = 0;
-    for (bool again = true; again;) {
+    for (bool resume = false;;) {
         ctx->env.graph_chunk = opts->graph_chunk;
-        rc = issue_ee_steps(ctx, t, prec, opts->m_max, opts->orth, constant, limit, done);
+        rc = issue_ee_steps(ctx, t, prec, opts->m_max, opts->orth, constant, limit, resume, ctx->hctl[0].steps);
         ctx->env.graph_chunk = 0;
         if (rc) return rc;
         if ((rc = read_heads(ctx, 1))) return rc;
-        again = resident_retry(ctx, &rc);
+        resume = resident_expired(ctx, &rc);
         if (rc) return rc;
-        done = ctx->hctl[0].steps;
+        if (!resume) break;
     }
     if ((rc = copy_out(ctx, m, 0, y))) return rc;
     const Ctl& h = ctx->hctl[0];
@@ -1722,18 +1746,18 @@ int ch_phiv(ch_ctx* ctx, const ch_problem* prob, const double* y, double* y_out,
     PartSeq ps = partials_of(b, t);
     ResidentLease lease;
     use_resident_cycles(ctx, t, m_max, CH_ORTH_DCGS2, 0, &lease);
+    HIP_TRY(ctx, launch_resid(t, prec, b, ps, b.ybuf[0], b.ybuf[0], false, true, ctx->stream));
+    HIP_TRY(ctx, launch_after_resid(t, b, ps, true, ctx->stream));
+    ctx->expect[0] += 1;
     for (bool again = true; again;) {
-        HIP_TRY(ctx, launch_resid(t, prec, b, ps, b.ybuf[0], b.ybuf[0], false, true, ctx->stream));
-        HIP_TRY(ctx, launch_after_resid(t, b, ps, true, ctx->stream));
-        ctx->expect[0] += 1;
         if ((rc = issue_cycle(ctx, t, prec, ps, b.ybuf[0], m_max, CH_ORTH_DCGS2))) return rc;
         HIP_TRY(ctx, launch_update(t, prec, b, b.ybuf[0], b.ybuf[1], true, ctx->stream));
         if (mode == CH_PHI_RESTART &&
             (rc = restart_cycles(ctx, t, prec, ps, b.ybuf[0], b.ybuf[1], m_max, CH_ORTH_DCGS2)))
             return rc;
         if ((rc = read_heads(ctx, 1))) return rc;
-        again = resident_retry(ctx, &rc);
-        if (rc) return rc;
+        again = resident_expired(ctx, &rc);
+        if (rc || (again && (rc = repeat_cycle(ctx, t, prec, ps, b.ybuf[0], b.ybuf[1])))) return rc;
     }
     const Ctl& h = ctx->hctl[0];
     if (h.status == CH_OK)

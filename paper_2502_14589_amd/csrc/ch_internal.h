@@ -266,6 +266,8 @@ bool all_cycles_done(const Table& t, const DevBuffers& b, const int* expected);
 // instance has reported the cycle finished (later launches would exit at once).
 hipError_t launch_arnoldi(const Table& t, int prec, const DevBuffers& b, PartSeq& ps, const double* y, int m_max,
                           int orth, const int* expected, const LaunchEnv* env, hipStream_t s);
+// Basis column 0 again from f(y^n) as kept (fcur), for a cycle that is repeated (single grids).
+hipError_t launch_start_vector(const Table& t, int prec, const DevBuffers& b, hipStream_t s);
 // unit: the basis is stored normalised (DCGS2)
 hipError_t launch_update(const Table& t, int prec, const DevBuffers& b, const double* y, double* ynew, bool unit,
                          hipStream_t s);

@@ -403,6 +403,12 @@ __global__ __launch_bounds__(CH_BLOCK) void k_dots_reduce(Ctl* __restrict__ ctls
     if (threadIdx.x == 0) ctl->dt[r] = tot[0];
 }
 
+// Basis column 0 from f(y^n) as kept, rounded as the passes that form f store it (single grids).
+template <typename TV>
+__global__ __launch_bounds__(CH_BLOCK) void k_start_vector(const double* __restrict__ f, TV* __restrict__ V0, long long N) {
+    for (long long i = (long long)blockIdx.x * CH_BLOCK + threadIdx.x; i < N; i += (long long)gridDim.x * CH_BLOCK) V0[i] = TV(f[i]);
+}
+
 // ---------------------------------------------------------------------------
 // y^{n+1} = y^n + V_j (beta u)  (the solution update of Fig. 3)
 // ---------------------------------------------------------------------------
@@ -1453,6 +1459,14 @@ hipError_t launch_arnoldi(const Table& t, int prec, const DevBuffers& b, PartSeq
         return e;
     }
     return hipSuccess;
+}
+
+hipError_t launch_start_vector(const Table& t, int prec, const DevBuffers& b, hipStream_t s) {
+    if (prec == CH_FP64)
+        hipLaunchKernelGGL((k_start_vector<double>), dim3(t.cgrid), dim3(CH_BLOCK), 0, s, b.fcur, static_cast<double*>(b.V), t.hinst[0].N);
+    else
+        hipLaunchKernelGGL((k_start_vector<float>), dim3(t.cgrid), dim3(CH_BLOCK), 0, s, b.fcur, static_cast<float*>(b.V), t.hinst[0].N);
+    return hipGetLastError();
 }
 
 hipError_t launch_update(const Table& t, int prec, const DevBuffers& b, const double* y, double* ynew, bool unit,

@@ -1,5 +1,7 @@
-"""Which launches a call takes: the counts of the context say which path ran, and a context kept to
-ordinary launches is the reference.  Their results agree bit for bit.
+"""Which launches a call takes, and what it does when a wait of a resident launch runs out
+part way: the counts of the context say which path ran, and a wait bound of zero
+from a chosen resident launch on makes that one give up.  The results equal those of ordinary
+launches bit for bit wherever the repeat falls.
 """
 import threading
 
@@ -62,6 +64,27 @@ def test_resident_against_ordinary_launches(n, kind, prec, what):
         info = c.resident_info()
         assert info["launches"] >= 1 and info["repeats"] == 0
         assert o.resident_info() == {"launches": 0, "repeats": 0}
+    assert got[1:] == ref[1:] and np.array_equal(got[0], ref[0])
+
+
+# the launch that gives up: of adaptive steps the first, second (odd) and third (even); of constant
+# steps and the phi action the first cycle, later cycles of a step and later steps
+@pytest.mark.parametrize("what,after", [("ee", 0), ("ee", 1), ("ee", 2), ("ee", 5), ("constant", 0), ("constant", 1), ("constant", 2),
+                                        ("constant", 5), ("constant", 7), ("lim", 0), ("lim", 1), ("lim", 2), ("phiv", 0),
+                                        ("phiv", 1), ("phiv", 3), ("shrink", 0)])
+@pytest.mark.parametrize("prec", [ch.CH_FP64, ch.CH_FP32_MIXED])
+def test_repeat_from_a_later_launch(what, after, prec):
+    say(f"repeat of {what} after {after} launches prec={prec}")
+    n = 96
+    p, rho = problem(n, "periodic", prec)
+    y0 = uniform_field(n, 2, 0.1, 0.4, seed=8900)
+    with ch.Context(0) as c, ch.Context(0) as o:
+        o.set_resident(False)
+        ref = call(o, what, p, rho, y0)
+        c.set_resident(True, 0, after)
+        got = call(c, what, p, rho, y0)
+        info = c.resident_info()
+        assert info["launches"] > after and info["repeats"] == 1
     assert got[1:] == ref[1:] and np.array_equal(got[0], ref[0])
 
 
