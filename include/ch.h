@@ -369,17 +369,20 @@ int ch_time_kernel(ch_ctx *ctx, const ch_problem *prob, int kernel, int m_max, c
  * Resident launches.  ch_run_ee, ch_step_ee, ch_phiv, ch_run_lim and ch_step_lim issue a whole
  * Krylov cycle, or all stages of a LIM step, of a single 2-D grid that fits the device as
  * one launch whose workgroups wait for each other.  Every wait is bounded: when one
- * runs out (the workgroups did not fit beside what else runs on the device), the launch ends and the
- * step is repeated with ordinary launches; the results are the same.
+ * runs out (the workgroups did not fit beside what else runs on the device), the launch ends, the
+ * cycle or step is repeated with ordinary launches, and the context keeps to those for 32 times the wait,
+ * twice as long after each further one that runs out; the results are the same.
  *
  * ch_set_resident: enabled 0 keeps the context to ordinary launches.  wait_us: the
- * longest wait in microseconds (0 .. 10^7; < 0: the built-in 500000; a new context takes it from the
+ * longest wait in microseconds (0 .. 10^7; < 0: the built-in 100000; a new context takes it from the
  * environment variable CH_RESIDENT_WAIT_US where that is set).  after: the context's next `after`
- * resident launches still have the bound before.  ch_get_resident: the context's counts.
+ * resident launches still have the bound before.  The call also ends a pause.  ch_get_resident: the
+ * context's counts.
  */
 typedef struct {
     long long launches;   /* resident launches issued */
     long long repeats;    /* those a wait of which ran out */
+    double paused_s;      /* seconds until the context issues them again (0: it does) */
 } ch_resident_info;
 
 int ch_set_resident(ch_ctx *ctx, int enabled, int wait_us, int after);

@@ -79,7 +79,7 @@ class ChRequest(ctypes.Structure):
 
 
 class ChResidentInfo(ctypes.Structure):
-    _fields_ = [("launches", c_longlong), ("repeats", c_longlong)]
+    _fields_ = [("launches", c_longlong), ("repeats", c_longlong), ("paused_s", c_double)]
 
     def as_dict(self):
         return {name: getattr(self, name) for name, _ in self._fields_}
@@ -363,7 +363,8 @@ class Context:
         self._raise(self.lib.ch_set_resident(self._ptr, int(bool(enabled)), int(wait_us), int(after)), "ch_set_resident")
 
     def resident_info(self) -> dict:
-        """{'launches': resident launches issued, 'repeats': those that gave up waiting}."""
+        """{'launches': resident launches issued, 'repeats': those that gave up waiting, 'paused_s': seconds
+        until they are issued again}."""
         out = ChResidentInfo()
         self._raise(self.lib.ch_get_resident(self._ptr, byref(out)), "ch_get_resident")
         return out.as_dict()

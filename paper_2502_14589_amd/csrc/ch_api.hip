@@ -29,6 +29,7 @@
 
 #include "ch_internal.h"
 #include "ch_march.h"
+#include "ch_pause.h"
 #include "ch_resident.h"
 
 // Copy of n values (a field to or from the pooled state).
@@ -56,6 +57,7 @@ struct ch_ctx {
         unsigned wait_us = CH_RES_WAIT_US;   // the wait bound of the launches after the next `after`
         int after = 0;
         long long launches = 0, repeats = 0;
+        ResidentPause pause;
     } res;
     CycleShape cyc{0, 0};    // resident Krylov cycles of the current call (strips = 0: ordinary launches)
     int phibig_slots = 0;    // slots of the phi scratch of orders above 48
@@ -363,6 +365,18 @@ int next_resident(ch_ctx* ctx, int count, int* epoch) {
     return CH_OK;
 }
 
+double now_s() {
+    return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
+}
+
+// Whether a call may issue resident launches, whether one gave up, and that all passed.
+bool resident_allowed(const ch_ctx* ctx) { return ctx->res.on && ctx->res.pause.over(now_s()); }
+
+void note_expiry(ch_ctx* ctx) {
+    ctx->res.repeats += 1;
+    ctx->res.pause.expired(now_s(), 1e-6 * ctx->b.wait_us);
+}
+
 struct Member {
     Shape sh;
     double eps;
@@ -636,7 +650,7 @@ int issue_cycle(ch_ctx* ctx, const Table& t, int prec, PartSeq& ps, const double
 // lease is held until the call returns.
 void use_resident_cycles(ch_ctx* ctx, const Table& t, int m_max, int orth, int graph_chunk, ResidentLease* lease) {
     ctx->cyc = CycleShape{0, 0};
-    if (!ctx->res.on || orth != CH_ORTH_DCGS2 || graph_chunk > 0) return;
+    if (orth != CH_ORTH_DCGS2 || graph_chunk > 0 || !resident_allowed(ctx)) return;
     const CycleShape c = cycle_shape(t, m_max, ctx->cus);
     if (c.strips > 0 && ensure_resident(ctx, true) == CH_OK && lease->take(ctx->device, ctx->cus, c.workgroups)) ctx->cyc = c;
 }
@@ -649,7 +663,7 @@ bool resident_expired(ch_ctx* ctx, int* rc) {
     *rc = CH_OK;
     if (h.status != CH_RES_RETRY) return false;
     ctx->cyc = CycleShape{0, 0};
-    ctx->res.repeats += 1;
+    note_expiry(ctx);
     h.status = CH_OK;
     h.halted = h.done = h.j = h.converged = h.traced = 0;
     h.cyc += 1;
@@ -874,6 +888,7 @@ int run_ee(ch_ctx* ctx, const ch_problem* prob, double* y, double tau0, double t
         if (rc) return rc;
         if (!resume) break;
     }
+    if (ctx->cyc.strips > 0) ctx->res.pause.passed();
     if ((rc = copy_out(ctx, m, 0, y))) return rc;
     const Ctl& h = ctx->hctl[0];
     const int nrec = std::min(h.steps, recs);
@@ -1038,8 +1053,11 @@ int issue_lim_resident(ch_ctx* ctx, const Table& t, const LimTiles& g, PartSeq& 
     Ctl& h = ctx->hctl[0];
     *s = h.steps;
     *done = h.status != CH_RES_RETRY;
-    if (*done) return CH_OK;
-    ctx->res.repeats += 1;
+    if (*done) {
+        ctx->res.pause.passed();
+        return CH_OK;
+    }
+    note_expiry(ctx);
     h.status = CH_OK;
     h.halted = 0;
     HIP_TRY(ctx, hipMemcpyAsync(b.ctl, &h, CTL_HEAD, hipMemcpyHostToDevice, ctx->stream));
@@ -1068,7 +1086,7 @@ int run_lim(ch_ctx* ctx, const ch_problem* prob, double* y, double tau0, double 
     long long s0 = 0;
     bool done = false;
     ResidentLease lease;   // held until the call returns: its stream has drained then
-    if (ctx->res.on && uses_strips(t)) {
+    if (uses_strips(t) && resident_allowed(ctx)) {
         const LimTiles g = lim_tiles(t.hinst[0], ctx->cus);
         if (g.rows > 0 && ensure_resident(ctx, false) == CH_OK && lease.take(ctx->device, ctx->cus, g.ntx * g.nty)) {
             if ((rc = issue_lim_resident(ctx, t, g, ps, max_steps, &s0, &done))) return rc;
@@ -1153,10 +1171,6 @@ void record_from_head(const Ctl& h, ch_step_record* out) {
 // ---------------------------------------------------------------------------
 // Serving: continuous batching (ch_server_create / ch_submit / ch_poll)
 // ---------------------------------------------------------------------------
-double now_s() {
-    return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch()).count();
-}
-
 struct Req {
     unsigned long long id = 0;
     int n = 0, steps = 0;
@@ -1601,6 +1615,7 @@ int ch_set_resident(ch_ctx* ctx, int enabled, int wait_us, int after) {
     ctx->res.on = enabled != 0;
     ctx->res.wait_us = wait_us < 0 ? CH_RES_WAIT_US : (unsigned)wait_us;
     ctx->res.after = after;
+    ctx->res.pause = ResidentPause{};
     return CH_OK;
 }
 
@@ -1608,6 +1623,7 @@ int ch_get_resident(ch_ctx* ctx, ch_resident_info* out) {
     if (!ctx || !out) return CH_EINVAL;
     out->launches = ctx->res.launches;
     out->repeats = ctx->res.repeats;
+    out->paused_s = std::max(0.0, ctx->res.pause.until - now_s());
     return CH_OK;
 }
 
@@ -1759,6 +1775,7 @@ int ch_phiv(ch_ctx* ctx, const ch_problem* prob, const double* y, double* y_out,
         again = resident_expired(ctx, &rc);
         if (rc || (again && (rc = repeat_cycle(ctx, t, prec, ps, b.ybuf[0], b.ybuf[1])))) return rc;
     }
+    if (ctx->cyc.strips > 0) ctx->res.pause.passed();
     const Ctl& h = ctx->hctl[0];
     if (h.status == CH_OK)
         HIP_TRY(ctx, hipMemcpyAsync(y_out, b.ybuf[1], sizeof(double) * sh.N, hipMemcpyDeviceToDevice, ctx->stream));

@@ -13,9 +13,10 @@
 //
 // Every wait ends: after `wait_us` of waiting a workgroup gives up, raises
 // the launch's failure word (which ends the others' waits) and the launch
-// marks the run as not done; the host then repeats the step with ordinary
-// launches.  The workgroups of a launch fit the device together because its
-// host call holds a lease on that many CUs (ResidentLease).
+// marks the run as not done; the host then repeats the cycle or step with ordinary
+// launches, and keeps to them for a while (ch_pause.h).  The workgroups of a launch fit the
+// device together because its host call holds a lease on that many CUs (ResidentLease).
+// The leases are this process's: another process on the device can make a wait run out.
 #pragma once
 
 #include "ch_internal.h"
@@ -34,7 +35,7 @@
 // Status a resident launch leaves in the control block (with halted set)
 // when a wait ran out: never returned to a caller.
 #define CH_RES_RETRY 1000
-#define CH_RES_WAIT_US 500000
+#define CH_RES_WAIT_US 100000     // some fifty cycles
 #define CH_RES_WAIT_MAX_US 10000000
 
 #ifdef __HIPCC__

@@ -63,7 +63,7 @@ def test_resident_against_ordinary_launches(n, kind, prec, what):
         got, ref = call(c, what, p, rho, y0), call(o, what, p, rho, y0)
         info = c.resident_info()
         assert info["launches"] >= 1 and info["repeats"] == 0
-        assert o.resident_info() == {"launches": 0, "repeats": 0}
+        assert o.resident_info() == {"launches": 0, "repeats": 0, "paused_s": 0.0}
     assert got[1:] == ref[1:] and np.array_equal(got[0], ref[0])
 
 
@@ -121,3 +121,31 @@ def test_launches_of_several_streams_share_the_device(n):
         t.join()
     assert not errors, errors
     assert sum(x["launches"] for x in infos) > 0 and sum(x["repeats"] for x in infos) == 0
+
+
+@pytest.mark.parametrize("what", ["ee", "lim", "shrink"])
+def test_an_expired_wait_is_remembered(what):
+    """After a wait has run out the following calls take ordinary launches, until the pause is over; twice as long
+    after the next one."""
+    import time
+
+    say(f"pause after an expired wait: {what}")
+    p, rho = problem(96, "periodic")
+    y0 = uniform_field(96, 2, 0.1, 0.4, seed=8960)
+    with ch.Context(0) as c:
+        call(c, what, p, rho, y0)   # workspaces
+        n0 = c.resident_info()["launches"]
+        c.set_resident(True, 0)
+        call(c, what, p, rho, y0)
+        first = c.resident_info()
+        assert first["launches"] > n0 and first["repeats"] == 1 and 0.0 < first["paused_s"] <= 0.32
+        call(c, what, p, rho, y0)
+        second = c.resident_info()
+        assert second["launches"] == first["launches"] and second["paused_s"] > 0.0
+        time.sleep(second["paused_s"] + 0.01)
+        call(c, what, p, rho, y0)
+        third = c.resident_info()
+        assert third["launches"] > first["launches"] and third["repeats"] == 2 and 0.32 < third["paused_s"] <= 0.64
+        c.set_resident(True)
+        call(c, what, p, rho, y0)
+        assert c.resident_info()["repeats"] == 2 and c.resident_info()["launches"] > third["launches"]
