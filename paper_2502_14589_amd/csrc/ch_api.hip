@@ -14,7 +14,6 @@
 #include <string.h>
 
 #include <algorithm>
-#include <atomic>
 #include <climits>
 #include <chrono>
 #include <condition_variable>
@@ -28,6 +27,7 @@
 #include <vector>
 
 #include "ch_internal.h"
+#include "ch_lease.h"
 #include "ch_march.h"
 #include "ch_pause.h"
 #include "ch_resident.h"
@@ -303,40 +303,6 @@ PartSeq partials_of(const DevBuffers& b, const Table& t) {
     ps.ld = (size_t)t.pld;
     return ps;
 }
-
-// CUs of each device held by resident launches (ch_resident.h) of this
-// process.  A call that issues such launches holds a lease on one CU per
-// workgroup until its stream has drained, so the workgroups of all leases on a
-// device fit it together and no launch waits for workgroups that cannot
-// start; a call that gets no lease issues ordinary launches (same results).
-class ResidentLease {
-    static constexpr int DEVICES = 64;
-    static std::atomic<int> used[DEVICES];
-    std::atomic<int>* u = nullptr;
-    int n = 0;
-
-public:
-    ResidentLease() = default;
-    ResidentLease(const ResidentLease&) = delete;
-    ResidentLease& operator=(const ResidentLease&) = delete;
-    ~ResidentLease() { release(); }
-    bool take(int device, int cus, int count) {
-        release();
-        if (device < 0 || device >= DEVICES || count < 1) return false;
-        if (used[device].fetch_add(count) + count > cus) {
-            used[device].fetch_sub(count);
-            return false;
-        }
-        u = &used[device];
-        n = count;
-        return true;
-    }
-    void release() {
-        if (u) u->fetch_sub(n);
-        u = nullptr;
-    }
-};
-std::atomic<int> ResidentLease::used[ResidentLease::DEVICES];
 
 // The words of the context's resident launches and the partials of its
 // resident Krylov cycles.

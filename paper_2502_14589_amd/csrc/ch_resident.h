@@ -15,7 +15,7 @@
 // the launch's failure word (which ends the others' waits) and the launch
 // marks the run as not done; the host then repeats the cycle or step with ordinary
 // launches, and keeps to them for a while (ch_pause.h).  The workgroups of a launch fit the
-// device together because its host call holds a lease on that many CUs (ResidentLease).
+// device together because its host call holds a lease on that many CUs (ch_lease.h).
 // The leases are this process's: another process on the device can make a wait run out.
 #pragma once
 
