@@ -372,6 +372,7 @@ int ch_time_kernel(ch_ctx *ctx, const ch_problem *prob, int kernel, int m_max, c
  * runs out (the workgroups did not fit beside what else runs on the device), the launch ends, the
  * cycle or step is repeated with ordinary launches, and the context keeps to those for 32 times the wait,
  * twice as long after each further one that runs out; the results are the same.
+ * A context on a stream with a CU mask takes ordinary launches only.
  *
  * ch_set_resident: enabled 0 keeps the context to ordinary launches.  wait_us: the
  * longest wait in microseconds (0 .. 10^7; < 0: the built-in 100000; a new context takes it from the

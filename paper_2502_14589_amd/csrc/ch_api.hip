@@ -50,7 +50,7 @@ struct ch_ctx {
     int slots = 0;           // control blocks allocated
     size_t rec_n = 0;        // step records allocated
     int part_ld = 0, dots_ld = 0;   // row lengths b.part and b.dots have room for
-    int cus = 0;             // compute units of the device
+    int cus = 0;             // compute units for resident launches (0: none, the stream has a CU mask)
     int epoch = 0;           // last flag value given to a resident launch
     struct {
         bool on = true;      // ch_set_resident
@@ -1494,6 +1494,18 @@ const int na_zero_map[NA_MAP] = {};
 // ---------------------------------------------------------------------------
 extern "C" {
 
+// True when a stream runs on fewer CUs than the device has.
+static bool masked(hipStream_t s, int cus) {
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(s, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    int n = 0;
+    for (uint32_t m : mask) n += __builtin_popcount(m);
+    return n > 0 && n < cus;
+}
+
 int ch_create(ch_ctx** out, int device, void* hip_stream) {
     if (!out) return CH_EINVAL;
     *out = nullptr;
@@ -1511,6 +1523,9 @@ int ch_create(ch_ctx** out, int device, void* hip_stream) {
         (void)hipGetLastError();
         ctx->cus = 0;
     }
+    // a stream with a CU mask: its CUs need not be spread evenly over the XCDs, as the
+    // workgroups are, so nothing is said about which of them fit together
+    if (masked(ctx->stream, ctx->cus)) ctx->cus = 0;
     // CH_RESIDENT_WAIT_US: how long a workgroup of a resident launch waits for
     // another before the step is repeated with ordinary launches
     const char* w = getenv("CH_RESIDENT_WAIT_US");

@@ -149,3 +149,29 @@ def test_an_expired_wait_is_remembered(what):
         c.set_resident(True)
         call(c, what, p, rho, y0)
         assert c.resident_info()["repeats"] == 2 and c.resident_info()["launches"] > third["launches"]
+
+
+def test_a_stream_with_a_cu_mask_takes_ordinary_launches():
+    """Its CUs are fewer than the device's, and not known to be spread over the XCDs as the workgroups are."""
+    import ctypes
+
+    import torch
+
+    say("stream with a CU mask")
+    hip = ch.load_library()   # its HIP runtime
+    stream = ctypes.c_void_p()
+    mask = (ctypes.c_uint32 * 8)(*[0xFFFFFFFF] * 4)
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), ctypes.c_uint32(8), mask) == 0
+    p, rho = problem(96, "periodic")
+    y0 = uniform_field(96, 2, 0.1, 0.4, seed=8970)
+    with ch.Context(0) as o:
+        o.set_resident(False)
+        ref = [call(o, what, p, rho, y0) for what in ("ee", "lim")]
+    s = torch.cuda.ExternalStream(stream.value)
+    with torch.cuda.stream(s):
+        with ch.Context(0) as c:
+            got = [call(c, what, p, rho, y0) for what in ("ee", "lim")]
+            assert c.resident_info()["launches"] == 0
+    s.synchronize()
+    for g, r in zip(got, ref):
+        assert g[1:] == r[1:] and np.array_equal(g[0], r[0])
