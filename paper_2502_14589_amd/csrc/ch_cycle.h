@@ -593,6 +593,9 @@ __device__ __forceinline__ void cycle_main(const CycleArgs& A, CycCoef& C, doubl
                 __builtin_amdgcn_s_sleep(1);
             }
         }
+        // The next reads of u are ordinary loads, which the relaxed polls do not order: the
+        // compiler is to keep them behind (the hardware does; no instruction).
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 }
 
