@@ -921,6 +921,21 @@ int read_head(ch_ctx* ctx, const DevBuffers& b, Ctl* h) {
     return CH_OK;
 }
 
+// Waits (at most CH_PLAN_WAIT_S) until every instance's pinned words hold the order of plan
+// launch `seq`, the last one issued; false: they do not.
+bool await_plan(const DevBuffers& b, const Table& t, int seq) {
+    if (!b.hlim) return false;
+    const auto t0 = std::chrono::steady_clock::now();
+    for (long long spin = 0;; ++spin) {
+        bool all = true;
+        for (int i = 0; i < t.ninst && all; ++i) all = b.hlim[2 * t.hinst[i].slot + 1] == seq;
+        if (all) return true;
+        if ((spin & 255) == 255 &&
+            std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() > CH_PLAN_WAIT_S)
+            return false;
+    }
+}
+
 // LIM step s of every instance of a table (Figs. 1 and 2): bounds of the
 // spectrum, the plan (whose Chebyshev orders the host reads to size the
 // stage launches: the largest order decides, instances of smaller order
@@ -945,28 +960,14 @@ int issue_lim_step(ch_ctx* ctx, const Table& t, const DevBuffers& b, PartSeq& ps
                               : launch_lim_stage(t, b, yin, yout, l, pairs, ctx->stream);
     };
     int nl = 0;
-    // every instance's order from the pinned words the plan writes (a
-    // bounded wait); else from copies of the control blocks
-    bool got = false;
-    if (b.hlim) {
-        const auto t0 = std::chrono::steady_clock::now();
-        for (long long spin = 0;; ++spin) {
-            bool all = true;
-            for (int i = 0; i < t.ninst && all; ++i) all = b.hlim[2 * t.hinst[i].slot + 1] == seq;
-            if (all) {
-                got = true;
-                break;
-            }
-            if ((spin & 255) == 255 &&
-                std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() > CH_PLAN_WAIT_S)
-                break;
+    // every instance's order from the pinned words the plan writes; else
+    // from copies of the control blocks
+    const bool got = await_plan(b, t, seq);
+    if (got)
+        for (int i = 0; i < t.ninst; ++i) {
+            const int p = b.hlim[2 * t.hinst[i].slot];
+            if (p > 0) nl = std::max(nl, lim_launches(p, pairs));
         }
-        if (got)
-            for (int i = 0; i < t.ninst; ++i) {
-                const int p = b.hlim[2 * t.hinst[i].slot];
-                if (p > 0) nl = std::max(nl, lim_launches(p, pairs));
-            }
-    }
     if (!got) {
         int lo = INT_MAX, hi = -1;
         for (int i = 0; i < t.ninst; ++i) {
@@ -991,18 +992,22 @@ int issue_lim_step(ch_ctx* ctx, const Table& t, const DevBuffers& b, PartSeq& ps
 }
 
 // LIM steps of a single grid with resident stage launches, from step *s on:
-// five launches per step and no host wait, since the stage launch reads the
-// Chebyshev order itself; the control block is read every 16 steps to see
-// whether the run has ended.  *s: the steps taken when it returns.
+// five launches per step and no copy back, since the stage launch reads the
+// Chebyshev order itself.  A run to a final time waits for each step's plan before it
+// issues the next step (the stages then still run) and stops at the plan that finds
+// it ended: a run of one step takes 205 us at 64^2, of twenty 1830; with
+// the control block read every 16 steps only, as other runs do, 304 and 1886.
+// *s: the steps taken when it returns.
 // *done: the run is over; otherwise a launch gave up waiting and step *s is
 // to be repeated with ordinary launches.
-int issue_lim_resident(ch_ctx* ctx, const Table& t, const LimTiles& g, PartSeq& ps, int max_steps, long long* s,
-                       bool* done) {
+int issue_lim_resident(ch_ctx* ctx, const Table& t, const LimTiles& g, PartSeq& ps, int max_steps, bool to_T,
+                       long long* s, bool* done) {
     const DevBuffers& b = ctx->b;
     int rc;
     for (long long k = *s;; ++k) {
         const bool last = max_steps > 0 && k >= max_steps;
-        if (last || (k % 16) == 15) {
+        const bool ended = to_T && k > *s && await_plan(b, t, ctx->lseq) && b.hlim[2 * t.hinst[0].slot] == 0;
+        if (last || ended || (k % 16) == 15) {
             if ((rc = read_heads(ctx, 1))) return rc;
             if (last || ctx->hctl[0].halted) break;
         }
@@ -1055,7 +1060,7 @@ int run_lim(ch_ctx* ctx, const ch_problem* prob, double* y, double tau0, double 
     if (uses_strips(t) && resident_allowed(ctx)) {
         const LimTiles g = lim_tiles(t.hinst[0], ctx->cus);
         if (g.rows > 0 && ensure_resident(ctx, false) == CH_OK && lease.take(ctx->device, ctx->cus, g.ntx * g.nty)) {
-            if ((rc = issue_lim_resident(ctx, t, g, ps, max_steps, &s0, &done))) return rc;
+            if ((rc = issue_lim_resident(ctx, t, g, ps, max_steps, T < INFINITY, &s0, &done))) return rc;
         }
     }
     for (long long s = s0; !done; ++s) {

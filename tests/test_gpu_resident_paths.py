@@ -175,3 +175,20 @@ def test_a_stream_with_a_cu_mask_takes_ordinary_launches():
     s.synchronize()
     for g, r in zip(got, ref):
         assert g[1:] == r[1:] and np.array_equal(g[0], r[0])
+
+
+@pytest.mark.parametrize("steps", [1, 2, 5, 17, 40])
+def test_lim_run_to_a_final_time_issues_few_steps_past_it(steps):
+    """A run of a few steps to T does not issue many more that find it ended."""
+    say(f"LIM to T in {steps} steps")
+    p, rho = problem(64, "periodic")
+    tau = 600.0 / rho
+    y0 = uniform_field(64, 2, 0.1, 0.4, seed=8980)
+    with ch.Context(0) as c, ch.Context(0) as o:
+        o.set_resident(False)
+        y, z = dev(y0), dev(y0)
+        st, _ = c.run_lim(p, y, tau, T=(steps - 0.5) * tau)
+        ref, _ = o.run_lim(p, z, tau, T=(steps - 0.5) * tau)
+        assert st == ref and st["steps"] == steps and st["t"] == (steps - 0.5) * tau
+        assert steps <= c.resident_info()["launches"] <= steps + 1
+    assert np.array_equal(y.cpu().numpy(), z.cpu().numpy())
