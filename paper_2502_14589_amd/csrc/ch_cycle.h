@@ -732,20 +732,16 @@ hipError_t launch_cycle_n(const Table& t, const CycleArgs& A, hipStream_t s) {
     return launch_cycle_v<TV, NW, S, 1>(t, A, s);
 }
 
-template <typename TV>
-hipError_t launch_cycle_p(const Table& t, int strips, const CycleArgs& A, hipStream_t s) {
-    switch (strips) {
-        case 4: return launch_cycle_n<TV, 4, 1>(t, A, s);
-        case 8: return launch_cycle_n<TV, 8, 1>(t, A, s);
-        case 12: return launch_cycle_n<TV, 12, 1>(t, A, s);
-        case 20: return launch_cycle_n<TV, 10, 2>(t, A, s);
-        default: return hipErrorInvalidValue;
-    }
-}
-
 }  // namespace
 
-// launch_cycle_p of one basis precision; each has a file of its own (the kernels
-// take a minute to compile).
-hipError_t launch_cycle_64(const Table& t, int strips, const CycleArgs& A, hipStream_t s);
-hipError_t launch_cycle_32(const Table& t, int strips, const CycleArgs& A, hipStream_t s);
+// The kernels of one basis precision and number of strips to a workgroup each have a file of their
+// own: they take most of a minute to compile together, and a first launch loads the code of
+// its file only (a process's first call 15.4 -> 14.5 ms at 64^2, of kernels in two files).
+hipError_t launch_cycle_64_4(const Table& t, const CycleArgs& A, hipStream_t s);
+hipError_t launch_cycle_64_8(const Table& t, const CycleArgs& A, hipStream_t s);
+hipError_t launch_cycle_64_12(const Table& t, const CycleArgs& A, hipStream_t s);
+hipError_t launch_cycle_64_20(const Table& t, const CycleArgs& A, hipStream_t s);
+hipError_t launch_cycle_32_4(const Table& t, const CycleArgs& A, hipStream_t s);
+hipError_t launch_cycle_32_8(const Table& t, const CycleArgs& A, hipStream_t s);
+hipError_t launch_cycle_32_12(const Table& t, const CycleArgs& A, hipStream_t s);
+hipError_t launch_cycle_32_20(const Table& t, const CycleArgs& A, hipStream_t s);

@@ -1,10 +1,5 @@
-// Resident Krylov cycles (ch_cycle.h): which grids take them, their launch, and
-// the FP64 kernels.
+// Resident Krylov cycles (ch_cycle.h): which grids take them, and their launch.
 #include "ch_cycle.h"
-
-hipError_t launch_cycle_64(const Table& t, int strips, const CycleArgs& A, hipStream_t s) {
-    return launch_cycle_p<double>(t, strips, A, s);
-}
 
 size_t cycle_doubles() { return (size_t)2 * CYC_PART + (size_t)(CH_MSMALL + 1) * CYC_WAVES * CYC_TOT; }
 
@@ -44,10 +39,13 @@ hipError_t launch_cycle(const Table& t, int prec, const DevBuffers& b, const Cyc
     A.G = c.workgroups - CYC_TESTS;
     A.m_max = m_max;
     A.wait_us = b.wait_us;
-    if (prec == CH_FP64) {
-        A.y = y;
-        return launch_cycle_64(t, c.strips, A, s);
+    const bool wide = prec == CH_FP64;
+    A.y = wide ? static_cast<const void*>(y) : b.y32;
+    switch (c.strips) {
+        case 4: return wide ? launch_cycle_64_4(t, A, s) : launch_cycle_32_4(t, A, s);
+        case 8: return wide ? launch_cycle_64_8(t, A, s) : launch_cycle_32_8(t, A, s);
+        case 12: return wide ? launch_cycle_64_12(t, A, s) : launch_cycle_32_12(t, A, s);
+        case 20: return wide ? launch_cycle_64_20(t, A, s) : launch_cycle_32_20(t, A, s);
+        default: return hipErrorInvalidValue;
     }
-    A.y = b.y32;
-    return launch_cycle_32(t, c.strips, A, s);
 }
