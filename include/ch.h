@@ -430,9 +430,10 @@ int ch_set_shape(ch_ctx *ctx, int dim, int n, int prec, const ch_shape *shape);
  * likewise, each over
  * Arnoldi iterations 1, m_max/2 and m_max - 1 (back-to-back launches under HIP
  * events, best of three), and keeps the fastest shape for later runs on this
- * context (as ch_set_shape).  *best: that shape; *best_us and *default_us: the
- * time of one matvec plus one update pass, averaged over those iterations, for
- * it and for the built-in choice.  Allocates the workspace of such a run and
+ * context (as ch_set_shape).  Where the built-in shape's Krylov cycles are resident, shapes
+ * that would take ordinary launches, or wider workgroups, are left out.
+ * *best: that shape; *best_us and *default_us: the time of one matvec plus one update
+ * pass, averaged over those iterations, for it and for the built-in choice.  Allocates the workspace of such a run and
  * overwrites its contents.
  */
 int ch_tune_shape(ch_ctx *ctx, const ch_problem *prob, int m_max, ch_shape *best, double *best_us,

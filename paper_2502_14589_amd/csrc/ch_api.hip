@@ -2003,12 +2003,28 @@ int ch_tune_shape(ch_ctx* ctx, const ch_problem* prob, int m_max, ch_shape* best
     } else {
         vxs.push_back(dflt.vx);
     }
+    // Strips per workgroup of the resident cycles under a shape (0: ordinary launches).  The
+    // launches timed here are the ordinary ones; where cycles are resident with the
+    // built-in shape, one that has none or wider workgroups is slower whatever they say
+    // (1400^2 FP32: 1024 workgroups instead of 1050, three steps 1986 -> 2150 us).
+    auto strips = [&](const ch_shape& c) {
+        Inst I = make_inst(Member{sh, prob->eps, prob->eyre, 0}, 0, dim, prec, 0, 0, 0);
+        I.vx = c.vx;
+        I.wblk = c.wblk;
+        Table t{};
+        t.ninst = 1;
+        t.dim = dim;
+        t.hinst = &I;
+        return ctx->res.on ? cycle_shape(t, m_max, ctx->cus).strips : 0;
+    };
+    const int built_in = strips(dflt);
     ch_shape bs = dflt;
     double bmv = INFINITY, dmv = INFINITY;
     for (int vx : vxs) {
         const int w0 = dim == 2 ? strip_blocks(n, vx) : dflt.wblk;
         for (int w : counts(w0)) {
             const ch_shape c{vx, w, dflt.cblk};
+            if (built_in > 0 && (strips(c) == 0 || strips(c) > built_in)) continue;
             double us;
             if ((rc = timed(c, CH_KERNEL_DC_MATVEC, &us))) {
                 restore();

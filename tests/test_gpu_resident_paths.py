@@ -192,3 +192,14 @@ def test_lim_run_to_a_final_time_issues_few_steps_past_it(steps):
         assert st == ref and st["steps"] == steps and st["t"] == (steps - 0.5) * tau
         assert steps <= c.resident_info()["launches"] <= steps + 1
     assert np.array_equal(y.cpu().numpy(), z.cpu().numpy())
+
+
+@pytest.mark.parametrize("n,prec", [(256, ch.CH_FP64), (1024, ch.CH_FP64), (1400, ch.CH_FP32_MIXED)])
+def test_a_tuned_shape_keeps_the_resident_cycles(n, prec):
+    """The tuner times ordinary launches; it does not keep a shape under which a run would have to take them."""
+    say(f"tuned shape n={n} prec={prec}")
+    p, rho = problem(n, "periodic", prec)
+    with ch.Context(0) as c:
+        c.tune_shape(p, m_max=30)
+        c.run_ee(p, dev(uniform_field(n, 2, 0.1, 0.4, seed=8990)), 90.0 / rho, max_steps=1, m_max=30)
+        assert c.resident_info()["launches"] == 1
