@@ -16,10 +16,13 @@ Forms: FP32-mixed (Krylov basis and stencils in FP32; state, reductions, phi,
 update and estimate in FP64) and plain FP64.  `value` is the FP32-mixed steps/s;
 the FP64 figures, the relative difference of the two states at T, the adaptive
 LIM at the same size, the 3-D 256^3 EE2 case and the batched and served forms
-are reported beside it.  The roofline figures come from back-to-back launches
-of the kernel over the Arnoldi iterations of every REPLAY_EVERY-th step of the
-timed run, timed by HIP events on the launching stream.  The CPU baseline is
-the FP64 NumPy/SciPy oracle on the first steps of the same workload.
+are reported beside it.  At this size a run issues each Krylov cycle as one
+resident launch (k_cycle), whose rate is the run's own (hbm_GBps_effective); the
+per-kernel and roofline figures are of the separate launches that batches and
+larger grids take: back-to-back launches over the Arnoldi iterations of
+every REPLAY_EVERY-th step of the timed run, timed by HIP events on the launching
+stream.  The CPU baseline is the FP64 NumPy/SciPy oracle on the first steps of
+the same workload.
 
     python bench.py [--steps K] [--warmup W] [--gpus 1]
         W untimed warm-up steps (a throw-away run from y0), then the timed
@@ -27,9 +30,9 @@ the FP64 NumPy/SciPy oracle on the first steps of the same workload.
     python bench.py --copy-calibration     (plain copy of known size, for the
                                             hardware-counter scale)
     python bench.py --counters             (FP32-mixed run to T, then the
-                                            replay of its dominant kernel, under
-                                            a symbol of its own that a profiler's
-                                            kernel filter selects)
+                                            replay of its matvecs as separate
+                                            launches, under a symbol of its own that
+                                            a profiler's kernel filter selects)
 """
 from __future__ import annotations
 
@@ -53,7 +56,7 @@ LIM_TAU0 = 2.5e-7
 C3_SIDE, C3_EPS, C3_TOL, C3_M, C3_SEED = 256, 0.02, 1e-6, 40, 2
 HBM_PEAK_GBPS = 8000.0
 METRIC = "CH time steps/s and HBM GB/s at 1024² (EE Krylov), FP32/batched vs FP64 plain"
-DOMINANT = "k_matvec_s (2-D row-strip DCGS2 Jacobian matvec with its 2j+2 basis dot products)"
+REPLAYED = "k_matvec_s (2-D row-strip DCGS2 Jacobian matvec with its 2j+2 basis dot products)"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "dc_matvec_1024sq_fp32_traffic.md")
 KERNEL_SOURCES = ("ch_strip.hip", "ch_rows.h", "ch_common.h", "ch_internal.h")
 
@@ -89,8 +92,8 @@ def dc_iters(recs, m_max: int):
 
 
 def replay(ctx, prob, kernel, m_max, iters=None, count=0):
-    """Back-to-back launches of one kernel (under a symbol of its own, so a
-    profiler reports them apart) over the given Arnoldi iterations or LIM
+    """Back-to-back separate launches of one kernel (under a symbol of its own,
+    so a profiler reports them apart) over the given Arnoldi iterations or LIM
     stage count, timed by two HIP events on the launching stream."""
     us, nbytes = ctx.time_kernel(prob, kernel, m_max, iters=iters, count=count)
     n = len(iters) if iters is not None else count
@@ -102,17 +105,19 @@ def run_ee_form(ctx, ch, torch, prob, y0, tau0, T, warmup, m_max, tol, fp32, N, 
                 replay_every=REPLAY_EVERY):
     """W warm-up steps (a throw-away run from y0: allocations, code objects),
     then the timed run from y0 until t = T (or max_steps), then back-to-back
-    launches of the DCGS2 kernels over the Arnoldi iterations of every
+    launches of the separate DCGS2 kernels over the Arnoldi iterations of every
     replay_every-th step, for the per-kernel figures.  Returns the figures and
     the final state."""
     ctx.run_ee(prob, torch.from_numpy(y0.copy()).to("cuda"), tau0, T=T, max_steps=max(warmup, 1), m_max=m_max,
                tol=tol)
     y = torch.from_numpy(y0.copy()).to("cuda")
+    before = ctx.resident_info()
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     st, recs = ctx.run_ee(prob, y, tau0, t0=0.0, T=T, max_steps=max_steps, m_max=m_max, tol=tol, records=True)
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
+    after = ctx.resident_info()
 
     w = 4 if fp32 else 8
     nbytes = sum(ee_step_bytes(r["j"], m_max, w, N, fp32) for r in recs)
@@ -133,6 +138,7 @@ def run_ee_form(ctx, ch, torch, prob, y0, tau0, T, warmup, m_max, tol, fp32, N, 
         "traced_frac": sum(r["traced"] for r in recs) / max(len(recs), 1),
         "matvecs_per_s": st["matvecs"] / dt, "sim_time_per_s": st["t"] / dt,
         "effective_GBps": nbytes / dt / 1e9, "kernels": kern,
+        "resident_cycles": after["launches"] - before["launches"], "repeated": after["repeats"] - before["repeats"],
         "replayed_steps": f"every {replay_every}th step of the timed run ({len(sample)} steps)",
         "replay_plan": {"dc_matvec": mv},
     }, y
@@ -151,19 +157,22 @@ def lim_form(ctx, ch, torch, y0, steps, warmup):
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
 
-    # the 2p - 1 stages of order p run as stage 0 alone, then p - 1 launches
-    # of two stages each: the pair launches of the timed steps, replayed
+    # the timed steps' stages are one resident launch each (k_lim_run); as separate
+    # launches (batches, larger grids) the 2p - 1 stages of order p are stage 0 alone, then
+    # p - 1 launches of two stages each: as many of those
     stage = replay(ctx, prob, ch.CH_KERNEL_LIM_STAGE2, 1, count=sum(r["j"] - 1 for r in recs))
     mean_p = sum(r["j"] for r in recs) / max(len(recs), 1)
     return {"workload": "adaptive LIM (Fig. 2), same 1024^2 field, FP64, tol 1e-4, tau0 = 2.5e-7",
             "steps_per_s": round(st["steps"] / dt, 3), "ms_per_step": round(1000.0 * dt / max(st["steps"], 1), 4),
             "mean_p": round(mean_p, 2), "matvecs_per_s": round(st["matvecs"] / dt, 1),
             "sim_time_per_s": (st["t"] - st_w["t"]) / dt,
-            "stage_roofline": {"kernel": "two LIM stages per launch (read y^n and z, write the second stage)",
+            "stage_roofline": {"kernel": "two LIM stages per launch (read y^n and z, write the second stage): the "
+                                         "separate launches; the timed steps are resident (k_lim_run)",
                                "bound": "hbm", "achieved": round(stage["achieved_GBps"], 1), "peak": HBM_PEAK_GBPS,
                                "unit": "GB/s", "frac": round(stage["achieved_GBps"] / HBM_PEAK_GBPS, 4),
                                "avg_launch_us": round(stage["avg_launch_us"], 3),
                                "bytes_per_launch": stage["bytes_per_launch"], "launches": stage["launches"]},
+            "timed_stage_us_at_most": round(1e6 * dt / max(sum(2 * r["j"] - 1 for r in recs), 1), 3),
             # the stage rate in the terms of the one-stage form (24 bytes per
             # point per stage): the bandwidth that form would need to match it
             "per_stage_us": round(stage["avg_launch_us"] / 2.0, 3),
@@ -275,8 +284,9 @@ def batched(ctx, ch, torch, steps: int = 50, sequential_sample: int = 8):
 def graph_issue(ctx, ch, torch):
     """Adaptive EE2 (FP32-mixed, Krylov dimension 30, tol 1e-4, tau0 1e-5) from
     y0 = 0.1 + U(-0.05, 0.05) at 128^2 (eps 0.02, 300 steps) and 1024^2 (eps
-    0.01, 100 steps), with every kernel launched directly and with each Krylov
-    cycle's iterations replayed from one captured graph (graph_chunk 31)."""
+    0.01, 100 steps): each Krylov cycle as one resident launch (the default), with
+    every kernel launched by itself, and with the iterations of a cycle replayed from one
+    captured graph (graph_chunk 31)."""
     from paper_2502_14589_amd.inputs import uniform_field
 
     out = {}
@@ -284,7 +294,8 @@ def graph_issue(ctx, ch, torch):
         prob = ch.Problem(2, n, eps, False, ch.CH_FP32_MIXED)
         y0 = torch.from_numpy(uniform_field(n, 2, 0.1, 0.05, seed=1)).to("cuda")
         res = {}
-        for chunk in (0, M_MAX + 1):
+        for form, chunk in (("resident", 0), ("direct", 0), ("graphs", M_MAX + 1)):
+            ctx.set_resident(form == "resident")
             ctx.run_ee(prob, y0.clone(), 1e-5, max_steps=steps, m_max=M_MAX, tol=TOL, graph_chunk=chunk)   # warm
             rates = []
             for _ in range(2):
@@ -294,7 +305,8 @@ def graph_issue(ctx, ch, torch):
                 ctx.run_ee(prob, y, 1e-5, max_steps=steps, m_max=M_MAX, tol=TOL, graph_chunk=chunk)
                 torch.cuda.synchronize()
                 rates.append(steps / (time.perf_counter() - t0))
-            res["graphs" if chunk else "direct"] = round(max(rates), 1)
+            res[form] = round(max(rates), 1)
+        ctx.set_resident(True)
         res["graph_vs_direct"] = round(res["graphs"] / res["direct"], 3)
         out[f"{n}x{n}"] = res
     out["unit"] = "steps/s (best of two runs)"
@@ -491,7 +503,7 @@ def kernel_source_sha() -> str:
 
 
 def measured_traffic(bytes_per_launch: float):
-    """HBM bytes per launch of the dominant kernel from the committed counter
+    """HBM bytes per launch of the replayed kernel from the committed counter
     summary, if it was taken on the current kernel sources and on the same
     replay (the same algorithmic bytes per launch, to 0.1%); else None."""
     try:
@@ -512,12 +524,13 @@ def measured_traffic(bytes_per_launch: float):
 
 def roofline(k, traffic=None):
     achieved = k["achieved_GBps"]
-    return {"bound": "hbm", "kernel": DOMINANT, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
+    return {"bound": "hbm", "kernel": REPLAYED, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": traffic,
             "bytes_per_launch": round(k["bytes_per_launch"], 1), "avg_launch_us": round(k["avg_launch_us"], 3),
             "launches": k["launches"],
-            "note": "back-to-back replay of the timed steps' working launches (same Arnoldi iterations), "
-                    "HIP events around the sequence on the launching stream"}
+            "note": "the separate launches of the path (batches, larger grids) over the timed steps' Arnoldi "
+                    "iterations, back to back, HIP events around the sequence on the launching stream; the timed "
+                    "run itself issues those iterations as resident cycles (k_cycle), see hbm_GBps_effective"}
 
 
 def cpu_baseline(y0, seconds: float):
@@ -583,7 +596,7 @@ def main():
     ap.add_argument("--cpu-seconds", type=float, default=15.0)
     ap.add_argument("--copy-calibration", action="store_true")
     ap.add_argument("--counters", action="store_true",
-                    help="FP32-mixed run to T, then the replay of its dominant kernel (its own symbol)")
+                    help="FP32-mixed run to T, then the replay of its matvecs as separate launches (their own symbol)")
     ap.add_argument("--plan-out", help="--counters: write the replay's Arnoldi iterations to this file")
     ap.add_argument("--plan-in", help="--counters: skip the run to T and replay the iterations of this file "
                                       "(a counter run then sees only one warm step and the replay)")
@@ -614,7 +627,7 @@ def main():
     workload = (f"2-D periodic Cahn-Hilliard 1024x1024, eps=0.01, y0=0.1+U(-0.05,0.05) seed 1, adaptive EE2 "
                 f"(Fig. 4) tol=1e-4, Krylov dim 30, tau0=1e-3, whole run from y0 to T={T:g}")
     if args.counters:
-        # the FP32-mixed run to T; the replay of its dominant kernel runs under
+        # the FP32-mixed run to T; the replay of its matvecs runs under
         # a symbol of its own, which a counter run selects by name
         prob = ch.Problem(2, N_SIDE, EPS, False, ch.CH_FP32_MIXED)
         with ch.Context(0) as ctx:
@@ -632,7 +645,7 @@ def main():
                 if args.plan_out:
                     with open(args.plan_out, "w") as fh:
                         json.dump({"dc_matvec": f["replay_plan"]["dc_matvec"], "replayed": replayed}, fh)
-        print(json.dumps({"mode": "counters", "kernel": DOMINANT, "source_sha": kernel_source_sha(),
+        print(json.dumps({"mode": "counters", "kernel": REPLAYED, "source_sha": kernel_source_sha(),
                           "workload": workload, "replayed": replayed, "replay": rep_mv}), flush=True)
         return
     if args.only_3d:
@@ -682,7 +695,8 @@ def main():
     def detail(f):
         return {"steps": f["steps"], "seconds": round(f["seconds"], 3), "t_end": f["t_end"],
                 "mean_j": round(f["mean_j"], 3), "frac_at_m_max": round(f["frac_at_m_max"], 4),
-                "traced_frac": round(f["traced_frac"], 4), "matvecs_per_s": round(f["matvecs_per_s"], 1),
+                "traced_frac": round(f["traced_frac"], 4), "resident_cycles": f["resident_cycles"],
+                "repeated": f["repeated"], "matvecs_per_s": round(f["matvecs_per_s"], 1),
                 "sim_time_per_s": f["sim_time_per_s"], "kernels": kern_summary(f),
                 "replayed": f["replayed_steps"]}
 
