@@ -230,10 +230,11 @@ __device__ __forceinline__ void cyc_all(const CycleArgs& A, CycCoef& C, int v) {
 }
 
 // Basis columns a wave keeps in registers, by the waves of a workgroup (four
-// waves leave 512 registers a lane, eight 256, twelve 168).  Eight columns of
-// twelve waves spill: 1290 -> 1050 us for three steps at 1024^2 FP32 with four.
-// With two strips to a wave (ten waves, 168) four columns spill more than they
-// save; two columns fit in LDS, and the others come from the last-level cache
+// waves leave 512 registers a lane, eight 256, twelve 168).  Four and eight waves
+// spill no vector registers; twelve spill 28 to 35 with four columns, and eight
+// columns are slower: 1290 us for three steps at 1024^2 FP32, 1050 with four.
+// With two strips to a wave (ten waves, 168 registers, 32 to 57 of them spilled without any
+// column) four columns cost more than they save; two columns fit in LDS, and the others come from the last-level cache
 // at about 9 TB/s, which is what bounds a cycle at 1024^2 FP64 (three steps 2270 us
 // as launches, 1860 here).  Five strips to each of four waves hold ten columns, but one
 // wave per SIMD hides no latency: 3950.

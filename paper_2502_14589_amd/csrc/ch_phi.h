@@ -22,8 +22,8 @@ namespace {
 // 970-989, applied to a Taylor instead of a Pade approximant).  T_19 is a
 // polynomial, so the evaluation is matrix products only -- no linear solve --
 // and all of them run on the FP64 matrix cores:
-//   X^2, X^3, X^4, X^5;  T_19 = B_0 + X^5 (B_1 + X^5 (B_2 + X^5 B_3)),
-//   B_i = sum_{q=0..4} X^q / (5i + q)!     (7 products),
+//   X^2, X^3, X^4;  T_19 = B_0 + X^4 (B_1 + X^4 (B_2 + X^4 (B_3 + X^4 B_4))),
+//   B_i = sum_{q=0..3} X^q / (4i + q)!     (7 products),
 // then q squarings.  Everything stays in LDS, in FP64.
 // ---------------------------------------------------------------------------
 // Orders are padded to a multiple of 16 for the matrix cores; the padding is

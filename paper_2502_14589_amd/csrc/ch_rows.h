@@ -1,6 +1,6 @@
-// Row-wise stencil arithmetic of the 2-D kernels (row strips, ch_strip.hip,
-// and the resident LIM stages, ch_resident.hip): a lane holds VX consecutive
-// columns of each row it touches.
+// Row-wise stencil arithmetic of the 2-D kernels (row strips, ch_strip.hip;
+// resident LIM stages, ch_resident.hip; resident Krylov cycles, ch_cycle.h): a
+// lane holds VX consecutive columns of each row it touches.
 #pragma once
 
 #include "ch_common.h"

@@ -50,16 +50,17 @@ inline int march_len_fp32(int n) {
 // estimate): 16 on large grids, down to 1 where 16 leave CUs without work.  A
 // plane step is a chain (a load, two stencil passes, the dot phase, a
 // barrier), so a grid that gives a CU one workgroup takes as long as its run:
-// 22 steps of 0.74 us in a LIM stage at L = 16, however small the grid.  More
+// 18 steps of about 0.9 us in a LIM stage at L = 16, however small the grid.  More
 // workgroups on a CU share its time: a step of w of them takes about
 // 0.55 + 0.19 w of these units (w <= 4, the occupancy), so the length that
 // minimises L + 4 (the two planes on either side) times that, summed over the
 // rounds of workgroups, is taken, the longer on ties (fewer rim planes).
-// Measured, EE2 step of 30 iterations and LIM step of 38 passes, L = 16 and
-// the length picked: 32^3 1760 -> 690 us and 750 -> 330; 97^3 2409 -> 1669
-// and 826 -> 598 (L = 4); 128^3 3343 -> 3023 and 829 -> 695 (4); 192^3 9862 ->
-// 9550 and 1548 -> 1497 (8).  From 2048 workgroups at L = 16 on (256^3) every
-// shorter length was slower.
+// Measured, EE2 step of dimension 30 with its trace and LIM step of order 19 (37
+// stages), L = 16 and the length picked: 32^3 2270 -> 907 us and 733 -> 324
+// (L = 1); 97^3 2769 -> 2053 and 743 -> 586 (4); 128^3 4189 -> 3817 and 811 ->
+// 704 (4); 160^3 7684 -> 7309 and 1193 -> 1063 (10); 192^3 12280 -> 11883 and
+// 1515 -> 1447 (14).  From 2048 workgroups at L = 16 on (256^3) every shorter
+// length was slower.  The rule is for a grid alone; batches group runs (march_group).
 inline int march_len_fp64(int n) {
     const unsigned nxy = (unsigned)((n + 63) / 64) * (unsigned)((n + 7) / 8);
     int best = CH_MARCH_L;
