@@ -1529,8 +1529,9 @@ int ch_create(ch_ctx** out, int device, void* hip_stream) {
         ctx->cus = 0;
     }
     // a stream with a CU mask: its CUs need not be spread evenly over the XCDs, as the
-    // workgroups are, so nothing is said about which of them fit together
-    if (masked(ctx->stream, ctx->cus)) ctx->cus = 0;
+    // workgroups are, so nothing is said about which of them fit together (the null
+    // stream has none; the query takes some 6 us)
+    if (ctx->stream && masked(ctx->stream, ctx->cus)) ctx->cus = 0;
     // CH_RESIDENT_WAIT_US: how long a workgroup of a resident launch waits for
     // another before the step is repeated with ordinary launches
     const char* w = getenv("CH_RESIDENT_WAIT_US");
