@@ -9,8 +9,8 @@ orthogonalisation) driven by the fused Jacobian stencil matvec, the
 small-matrix phi with the residual-time trace, the solution update and the
 error estimate / step controller (whose stencil also yields the next start
 vector).  The timed region is the whole run to T: the adaptive controller,
-not --steps, fixes how many steps that is (about 15000, nearly all at the
-largest Krylov dimension with a trace).
+not --steps, fixes how many steps that is (about 4900, two thirds of them at
+the largest Krylov dimension with a trace).
 
 Forms: FP32-mixed (Krylov basis and stencils in FP32; state, reductions, phi,
 update and estimate in FP64) and plain FP64.  `value` is the FP32-mixed steps/s;
